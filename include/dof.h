@@ -143,7 +143,9 @@ typedef struct {
      * trace_grab: rays a wave takes from the traversal's work counters at a
      * time, 1..256 (default 64).  trace_refill: idle lanes at which a wave takes
      * new rays, 1..64 (default 16).  trace_leaf_batch: lanes with a pending
-     * leaf at which a wave runs its triangle tests, 1..64 (default 32).
+     * leaf at which a wave runs its triangle tests, 1..64 (default 32; 1 also
+     * keeps the last rays of a launch each to its own lane, so that the
+     * counters of dof_stats follow from the rays alone).
      * trace_order: the order in which the persistent traversal hands out the
      * rays of the queue (row-major pixels): 1 from the first ray, 2 (and the
      * default 0) from the last -- the bottom image rows first, which in

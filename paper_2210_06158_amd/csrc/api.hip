@@ -857,7 +857,9 @@ dof_status dof_render_frame(dof_scene *scene, const dof_camera *cam, const dof_l
     }
     const dof::SideStream *side = (ev == nullptr && scene->side_ready) ? &scene->side : nullptr;
     DOF_HIP(dof::launch_frame_pre(fc, gather_rings(*lens, *p), L, scr, *gb, hin, hist->out, out->mask, ev, side, s));
-    const int blocks = p->trace_blocks > 0 ? p->trace_blocks : default_trace_blocks(false, fc.tk.stack, fc.tk.steps);
+    const int blocks = p->trace_blocks > 0 ? p->trace_blocks
+                                           : dof::blocks_for(default_trace_blocks(false, fc.tk.stack, fc.tk.steps),
+                                                             (int64_t)fc.hw * fc.hh * fc.m);
     DOF_HIP(dof::launch_trace(scene->dev, fc, L, scr, blocks, s));
     DOF_HIP(dof::launch_frame_post(scene->dev, fc, rings, L, scr, *gb, hin, hist->out, out->mask, *out, ev, side, s));
     scene->timed_frame = ev != nullptr;

@@ -18,10 +18,10 @@ constexpr float kSqrt2 = 1.41421356237f;  // one pixel diagonal (3.1.1, 3.3)
 constexpr int kTile = 16;                 // neighbourhood-max tile side
 constexpr int kRingTaps = 81;             // 1 + 8 + 16 + 24 + 32 (3.1.1)
 constexpr int kMaxBlades = 16;
-constexpr int kStackLds = 24;             // default traversal stack entries per lane (LDS only; deeper
+constexpr int kStackLds = 24;              // default traversal stack entries per lane (LDS only; deeper
                                           // work is found again through parent links); 16 and 32 also built
 constexpr int kTB = 128;                  // threads per traversal block
-constexpr int kTraceSteps = 4;            // default node visits per lane in one traversal loop iteration
+constexpr int kTraceSteps = 4;             // default node visits per lane in one traversal loop iteration
 constexpr int kMaxTraceBlocks = 4096;     // persistent traversal grid limit
 
 // ---------------------------------------------------------------- scene
@@ -272,6 +272,7 @@ hipError_t launch_build_bvh(SceneDev &s, hipStream_t st);
 
 // trace.hip
 int trace_blocks_per_cu(bool batch, int stack, int steps);   // resident blocks of the lens-ray traversal per CU
+int blocks_for(int blocks, int64_t rays);   // of `blocks`, as many as a launch of at most `rays` rays has work for
 hipError_t launch_trace(const SceneDev &s, const FrameConst &fc, const ScratchLayout &L, char *scratch,
                         int blocks, hipStream_t st);
 // the ray records of every thin-lens ray of the frame (after the compaction)

@@ -14,12 +14,16 @@
 // empty, so long rays do not hold a whole wave hostage (persistent threads
 // with dynamic fetch).  The runs are dealt over eight device counters 256 B
 // apart (run g by counter g mod 8), so the takes of all waves do not queue
-// on one address: with a single counter they did, and a 1080p frame's
-// traversal ran 10 % longer.  Thin-lens rays come from a generation kernel as
-// 24-byte records (origin and direction); a lane that takes one derives the
-// watertight test's shear and the slab reciprocals itself.  A finishing ray
-// leaves one 8-byte (leaf, t) record that the resolve expands when it shades,
-// so no lane waits on scene loads for shading.
+// on one address.  A launch with no more rays than lanes deals them evenly
+// over its waves instead.  When no ray is left to hand out and at most half of
+// a wave's lanes have one, the idle lanes share the others' rays, a pending
+// subtree each: the end of a launch, and all of a small one, is then bound by
+// the tree's depth and not by a ray's number of visits.  Thin-lens rays come
+// from a generation kernel as 24-byte records (origin and direction); a lane
+// that takes one derives the watertight test's shear and the slab reciprocals
+// itself.  A finishing ray leaves its hit's leaf and distance (8 bytes) that
+// the resolve or the G-buffer's shading expands, so no lane waits on scene
+// loads for shading.
 //
 // Closest hit: binary radix tree; the traversal reads a 32-byte copy of each
 // node holding both children's boxes in binary16, rounded outward (one fetch
@@ -31,7 +35,7 @@
 // distances compared as when it was first visited) whose far child still
 // passes the box test, that far child is the next subtree.  Every dropped
 // entry is such a far child, and the box test only loses children as the
-// best hit shrinks, so the walk visits exactly the pending subtrees that can
+// best hit shrinks, so the walk visits at least the pending subtrees that can
 // still hold the closest hit: any depth is exact with no memory beyond LDS.
 // Each outer iteration advances a lane by up to three or four nodes (a launch
 // knob), which spreads the wave-wide refill and batching decisions over
@@ -53,13 +57,18 @@ SceneArgs scene_args(const SceneDev &s) { return SceneArgs{s.nleaf, s.tris, s.al
 
 __device__ inline float pick3(float x, float y, float z, int k) { return k == 0 ? x : (k == 1 ? y : z); }
 
+// Entries of the ray's stack were dropped (found again through parent links).
+constexpr uint32_t kDropped = 0x80000000u;
+
 struct WRay {
     float o0, o1, o2;
-    int kx, ky, kz;
     float sx, sy, sz;
     float ix, iy, iz;   // slab reciprocals (zero components replaced by 1e-20)
     float cnx, cny, cnz, cfx, cfy, cfz;   // slab offsets of the entry and exit planes (box_hit)
-    uint32_t swx, swy, swz;               // 16 where the entry plane is a node word's high half, else 0
+    // bits 0-4: 16 where the axis' entry plane is a node word's high half, else
+    // 0 (a rotation reads no more of its count); bits 5-6 the watertight test's
+    // axes: kx in swx, ky in swy, kz in swz; bit 31 of swx: kDropped
+    uint32_t swx, swy, swz;
 };
 
 // The watertight test's axes: kz the largest direction component, kx and ky
@@ -95,9 +104,9 @@ __device__ inline void slab_offsets(WRay &r)
     const float cly = slab_offset(r.o1, r.iy, true), chy = slab_offset(r.o1, r.iy, false);
     const float clz = slab_offset(r.o2, r.iz, true), chz = slab_offset(r.o2, r.iz, false);
     const bool px = r.ix > 0.0f, py = r.iy > 0.0f, pz = r.iz > 0.0f;
-    r.cnx = px ? clx : chx; r.cfx = px ? chx : clx; r.swx = px ? 0u : 16u;
-    r.cny = py ? cly : chy; r.cfy = py ? chy : cly; r.swy = py ? 0u : 16u;
-    r.cnz = pz ? clz : chz; r.cfz = pz ? chz : clz; r.swz = pz ? 0u : 16u;
+    r.cnx = px ? clx : chx; r.cfx = px ? chx : clx; r.swx |= px ? 0u : 16u;
+    r.cny = py ? cly : chy; r.cfy = py ? chy : cly; r.swy |= py ? 0u : 16u;
+    r.cnz = pz ? clz : chz; r.cfz = pz ? chz : clz; r.swz |= pz ? 0u : 16u;
 }
 
 __device__ inline WRay make_wray(const float o[3], const float d[3])
@@ -107,7 +116,7 @@ __device__ inline WRay make_wray(const float o[3], const float d[3])
     int kx, ky, kz;
     wray_axes(d, kx, ky, kz);
     float dz = pick3(d[0], d[1], d[2], kz);
-    r.kx = kx; r.ky = ky; r.kz = kz;
+    r.swx = (uint32_t)kx << 5; r.swy = (uint32_t)ky << 5; r.swz = (uint32_t)kz << 5;
     r.sx = pick3(d[0], d[1], d[2], kx) / dz;
     r.sy = pick3(d[0], d[1], d[2], ky) / dz;
     r.sz = 1.0f / dz;
@@ -120,16 +129,17 @@ __device__ inline WRay make_wray(const float o[3], const float d[3])
 
 __device__ inline bool tri_hit(const WRay &r, float4 v0, float4 v1, float4 v2, float &tout)
 {
+    const int kx = (int)(r.swx >> 5 & 3u), ky = (int)(r.swy >> 5), kz = (int)(r.swz >> 5);
     float A0 = v0.x - r.o0, A1 = v0.y - r.o1, A2 = v0.z - r.o2;
     float B0 = v1.x - r.o0, B1 = v1.y - r.o1, B2 = v1.z - r.o2;
     float C0 = v2.x - r.o0, C1 = v2.y - r.o1, C2 = v2.z - r.o2;
-    float Akz = pick3(A0, A1, A2, r.kz), Bkz = pick3(B0, B1, B2, r.kz), Ckz = pick3(C0, C1, C2, r.kz);
-    float Ax = pick3(A0, A1, A2, r.kx) - r.sx * Akz;
-    float Ay = pick3(A0, A1, A2, r.ky) - r.sy * Akz;
-    float Bx = pick3(B0, B1, B2, r.kx) - r.sx * Bkz;
-    float By = pick3(B0, B1, B2, r.ky) - r.sy * Bkz;
-    float Cx = pick3(C0, C1, C2, r.kx) - r.sx * Ckz;
-    float Cy = pick3(C0, C1, C2, r.ky) - r.sy * Ckz;
+    float Akz = pick3(A0, A1, A2, kz), Bkz = pick3(B0, B1, B2, kz), Ckz = pick3(C0, C1, C2, kz);
+    float Ax = pick3(A0, A1, A2, kx) - r.sx * Akz;
+    float Ay = pick3(A0, A1, A2, ky) - r.sy * Akz;
+    float Bx = pick3(B0, B1, B2, kx) - r.sx * Bkz;
+    float By = pick3(B0, B1, B2, ky) - r.sy * Bkz;
+    float Cx = pick3(C0, C1, C2, kx) - r.sx * Ckz;
+    float Cy = pick3(C0, C1, C2, ky) - r.sy * Ckz;
     float U = Cx * By - Cy * Bx;
     float V = Ax * Cy - Ay * Cx;
     float W = Bx * Ay - By * Ax;
@@ -383,12 +393,11 @@ __device__ inline void put_ray(float4 *rec0, float2 *rec1, uint32_t r, const flo
     rec1[r] = make_float2(d[1], d[2]);
 }
 
-__device__ inline void get_ray(const float4 *rec0, const float2 *rec1, uint32_t r, float o[3], float d[3], WRay &w)
+__device__ inline void get_ray(const float4 *rec0, const float2 *rec1, uint32_t r, WRay &w)
 {
     const float4 a = rec0[r];
     const float2 b = rec1[r];
-    o[0] = a.x; o[1] = a.y; o[2] = a.z;
-    d[0] = a.w; d[1] = b.x; d[2] = b.y;
+    const float o[3] = {a.x, a.y, a.z}, d[3] = {a.w, b.x, b.y};
     w = make_wray(o, d);
 }
 
@@ -414,24 +423,21 @@ __device__ inline void ray_of(const SceneArgs &S, const Planes &P, uint32_t r, f
 }
 
 struct LensRays {
-    static constexpr bool kPerLaneScene = false;
+    static constexpr bool kPerLaneScene = false, kStats = true;
     const float4 *rec0;
     const float2 *rec1;
     uint2 *ray_lt;
 
-    __device__ void start(uint32_t r, float o[3], float d[3], WRay &w) const { get_ray(rec0, rec1, r, o, d, w); }
+    __device__ void start(uint32_t r, WRay &w) const { get_ray(rec0, rec1, r, w); }
 
-    __device__ void finish(const SceneArgs &, uint32_t r, const float *, const float *, const Hit &h) const
-    {
-        put_lt(ray_lt, r, h);
-    }
+    __device__ void finish(uint32_t r, const Hit &h) const { put_lt(ray_lt, r, h); }
 };
 
 // Lens rays of all frames of a batch: ray r belongs to the last job whose
 // first ray is at or before r (found in an LDS copy of the jobs' first rays);
 // each lane remembers its ray's job and traces against that job's scene.
 struct BatchRays {
-    static constexpr bool kPerLaneScene = true;
+    static constexpr bool kPerLaneScene = true, kStats = true;
     const Job *jobs;
     const BatchHead *head;
     int njobs;
@@ -463,72 +469,87 @@ struct BatchRays {
 
     __device__ SceneArgs scene(int j) const { return jobs[j].scene; }
 
-    __device__ void start(uint32_t r, int j, float o[3], float d[3], WRay &w) const
+    __device__ void start(uint32_t r, int j, WRay &w) const
     {
         const Job &J = jobs[j];
-        get_ray(J.P.rec0, J.P.rec1, r - offsets()[j], o, d, w);
+        get_ray(J.P.rec0, J.P.rec1, r - offsets()[j], w);
     }
 
-    __device__ void finish(const SceneArgs &, uint32_t r, int j, const float *, const float *, const Hit &h) const
+    __device__ void finish(uint32_t r, int j, const Hit &h) const
     {
         put_lt(jobs[j].P.ray_lt, r - offsets()[j], h);
     }
 };
 
+// A pinhole ray leaves its hit's leaf and distance in the pixel's own outputs
+// (the first word of its normal, its depth); k_gbuffer_shade turns them into
+// the G-buffer, so no lane of the traversal waits on scene loads for shading.
 struct PinholeRays {
-    static constexpr bool kPerLaneScene = false;
-    FrameConst fc;
-    SceneShade shade;
-    void *colour;
-    int cfmt;
+    static constexpr bool kPerLaneScene = false, kStats = false;
+    ViewConst view;
+    int32_t W, H;
     float *depth;
-    void *normal;
-    int nfmt;
-
-    __device__ void start(uint32_t p, float o[3], float d[3], WRay &w) const
-    {
-        setup(p, o, d);
-        w = make_wray(o, d);
-    }
+    uint32_t *normal;
+    uint32_t stride;   // words per pixel of the normal image
 
     __device__ void setup(uint32_t p, float o[3], float d[3]) const
     {
-        const int x = (int)(p % (uint32_t)fc.W), y = (int)(p / (uint32_t)fc.W);
+        const int x = (int)(p % (uint32_t)W), y = (int)(p / (uint32_t)W);
         float fv[3];
-        pixel_dir(fc.cur, x, y, fc.W, fc.H, fv);
+        pixel_dir(view, x, y, W, H, fv);
         float len = sqrtf((fv[0] * fv[0] + fv[1] * fv[1]) + fv[2] * fv[2]);
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             d[a] = fv[a] / len;
-            o[a] = fc.cur.pos[a];
+            o[a] = view.pos[a];
         }
     }
 
-    __device__ void finish(const SceneArgs &S, uint32_t p, const float o[3], const float d[3], const Hit &h) const
+    __device__ void start(uint32_t p, WRay &w) const
     {
-        if (h.id != ~0u) {
-            float P0 = o[0] + h.t * d[0], P1 = o[1] + h.t * d[1], P2 = o[2] + h.t * d[2];
-            Shaded s = dof::shade(S, shade, h.leaf, d);
-            st_rgba(colour, cfmt, p, make_float4(s.r, s.g, s.b, 1.0f));
-            depth[p] = ((P0 - fc.cur.pos[0]) * fc.cur.fwd[0] + (P1 - fc.cur.pos[1]) * fc.cur.fwd[1]) +
-                       (P2 - fc.cur.pos[2]) * fc.cur.fwd[2];
-            st_rgba(normal, nfmt, p, make_float4(s.n0, s.n1, s.n2, 0.0f));
-        } else {
-            st_rgba(colour, cfmt, p, make_float4(shade.sky[0], shade.sky[1], shade.sky[2], 1.0f));
-            depth[p] = INFINITY;
-            st_rgba(normal, nfmt, p, make_float4(0.0f, 0.0f, 0.0f, 0.0f));
-        }
+        float o[3], d[3];
+        setup(p, o, d);
+        w = make_wray(o, d);
+    }
+
+    __device__ void finish(uint32_t p, const Hit &h) const
+    {
+        depth[p] = h.t;
+        normal[(size_t)p * stride] = h.id == ~0u ? ~0u : h.leaf;
     }
 };
 
+__global__ __launch_bounds__(256) void k_gbuffer_shade(SceneArgs S, SceneShade sh, PinholeRays src, void *colour, int cfmt,
+                                                       int nfmt, uint32_t npx)
+{
+    const uint32_t p = blockIdx.x * 256u + threadIdx.x;
+    if (p >= npx) return;
+    const uint32_t leaf = src.normal[(size_t)p * src.stride];
+    if (leaf != ~0u) {
+        float o[3], d[3];
+        src.setup(p, o, d);
+        const float t = src.depth[p];
+        const ViewConst &v = src.view;
+        const float P0 = o[0] + t * d[0], P1 = o[1] + t * d[1], P2 = o[2] + t * d[2];
+        const Shaded s = dof::shade(S, sh, leaf, d);
+        st_rgba(colour, cfmt, p, make_float4(s.r, s.g, s.b, 1.0f));
+        src.depth[p] = ((P0 - v.pos[0]) * v.fwd[0] + (P1 - v.pos[1]) * v.fwd[1]) + (P2 - v.pos[2]) * v.fwd[2];
+        st_rgba(src.normal, nfmt, p, make_float4(s.n0, s.n1, s.n2, 0.0f));
+    } else {   // the depth holds the miss's infinite distance
+        st_rgba(colour, cfmt, p, make_float4(sh.sky[0], sh.sky[1], sh.sky[2], 1.0f));
+        st_rgba(src.normal, nfmt, p, make_float4(0.0f, 0.0f, 0.0f, 0.0f));
+    }
+}
+
 struct RawRays {
-    static constexpr bool kPerLaneScene = false;
+    static constexpr bool kPerLaneScene = false, kStats = false;
     const float *org, *dir;
     int32_t *hit;
     float *t;
 
-    __device__ void start(uint32_t i, float o[3], float d[3], WRay &w) const
+    __device__ void start(uint32_t i, WRay &w) const
     {
+        float o[3], d[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             o[a] = org[3 * (size_t)i + a];
@@ -537,7 +558,7 @@ struct RawRays {
         w = make_wray(o, d);
     }
 
-    __device__ void finish(const SceneArgs &, uint32_t i, const float *, const float *, const Hit &h) const
+    __device__ void finish(uint32_t i, const Hit &h) const
     {
         hit[i] = h.id == ~0u ? -1 : (int32_t)h.id;
         t[i] = h.t;
@@ -548,7 +569,7 @@ struct RawRays {
 // a chunk is sample k = r mod spp of full-res pixel p0 + r / spp, traced at
 // full resolution with the frame's lens; its (leaf, t) result goes to lt[r].
 struct RefRays {
-    static constexpr bool kPerLaneScene = false;
+    static constexpr bool kPerLaneScene = false, kStats = false;
     FrameConst fc;
     uint32_t p0, spp;
     uint2 *lt;
@@ -558,16 +579,14 @@ struct RefRays {
         thin_lens_ray(fc, p0 + r / spp, (uint32_t)fc.W, (uint32_t)fc.H, r % spp, o, d);
     }
 
-    __device__ void start(uint32_t r, float o[3], float d[3], WRay &w) const
+    __device__ void start(uint32_t r, WRay &w) const
     {
+        float o[3], d[3];
         ray(r, o, d);
         w = make_wray(o, d);
     }
 
-    __device__ void finish(const SceneArgs &, uint32_t r, const float *, const float *, const Hit &h) const
-    {
-        put_lt(lt, r, h);
-    }
+    __device__ void finish(uint32_t r, const Hit &h) const { put_lt(lt, r, h); }
 };
 
 // Mean shaded colour of each pixel's spp rays of a chunk (binary64 sum in
@@ -750,6 +769,9 @@ int gen_blocks(int64_t max_rays)
 
 // ---------------------------------------------------------------- persistent traversal
 
+constexpr int kShareRows = 6;    // LDS stack rows that the work sharing's state takes
+constexpr int kShareLanes = 32;  // busy lanes at which a wave without further rays starts to share
+constexpr int kShareSteps = 2;   // node visits per lane between two shares
 constexpr int kDropChunk = 8;    // oldest stack entries dropped when the LDS stack is full
 // Launch knobs (TraceKnobs, defaults in brackets): a wave refills when at
 // least tk.refill lanes are idle [16], takes tk.grab rays from the work
@@ -764,28 +786,56 @@ constexpr int kDropChunk = 8;    // oldest stack entries dropped when the LDS st
 // work: slot 0 of the work-counter slots; stats and drops_out (or null):
 // slot 0's node-visit and stack-drop statistics, a wave adding its totals to
 // the slot of its block (b mod kWorkParts) when it finishes.
-// Occupancy: at 77 VGPRs a lane, six waves fit a SIMD; with the 16-entry
-// stack the LDS would hold ten, and asking for seven (72 VGPRs, two spilled)
-// lets 14 instead of 12 blocks share a compute unit -- 4 % less traversal
-// time at 3840x2160, the same at 1920x1080.  A batch's lanes also hold their
-// scene's pointers (84 VGPRs: five waves); asking for six (80, none spilled)
-// makes a 32-session batch 3.6 % faster.  The 32-entry stack is LDS-bound
-// below both.
-template <class Src, int kStack, int kSteps>
+// What bounds it: at 3840x2160 the L1's lookups (0.9 a cycle and CU, the
+// texture data unit busy 0.95 of the time); at 1920x1080, with 2.4 rays per
+// lane, also the waves' uneven ends.  A visit takes about 50 vector
+// instructions, where predicates kept as booleans in registers, index
+// arithmetic for the stack and 64-bit node addresses made it 74: gathered over
+// the launch 763 M instead of 949 M vector instructions at 4K, the traversal
+// 1358 -> 1215 us there and 349 -> 240 us at 1080p (with the work sharing).
+// Occupancy: 70 VGPRs a lane would let seven waves share a SIMD; the 24-entry
+// stack's LDS allows six (12.5 KB a block), the 16-entry one's seven.  A
+// batch's lanes also hold their scene's pointers; asking for six waves (80
+// VGPRs, none spilled) makes a 32-session batch 3.6 % faster.
+// Orders a wave's own LDS accesses (they execute in order; this keeps the
+// compiler from moving or caching them).
+__device__ inline void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+typedef __attribute__((address_space(3))) uint32_t LdsWord;
+
+__device__ inline LdsWord *lds_word(uint32_t address) { return (LdsWord *)(uintptr_t)address; }
+
+// A lane mask as each lane's predicate.
+__device__ inline bool lanes(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
+
+// kFar: the nodes' byte offsets need more than 32 bits (kMaxNear leaves)
+template <class Src, int kStack, int kSteps, bool kFar>
 __global__ __launch_bounds__(kTB) __attribute__((amdgpu_waves_per_eu(Src::kPerLaneScene ? (kStack == 32 ? 1 : 6) : (kStack == 16 ? 7 : 1))))
 void k_traverse(SceneArgs S, Src src, uint32_t count, const uint32_t *count_ptr,
                                                   uint32_t *work, unsigned long long *stats, uint32_t *drops_out,
                                                   TraceKnobs tk)
 {
-    static_assert(kDropChunk < kStack, "a drop must leave room for the push");
-    __shared__ uint32_t lds_stack[kStack * kTB];
+    constexpr uint32_t kRow = kTB * sizeof(uint32_t);   // bytes from one stack row to the next
+    // The stack's fullness is looked at once per iteration, before its kSteps
+    // visits push at most one entry each: entries are dropped above kRows -
+    // kSteps.  The small stack gets rows for those pushes on top (20 rows and
+    // seven waves still fit the LDS); with 12 entries a 1080p frame dropped so
+    // often that it took 797 instead of 508 us.
+    constexpr int kRows = kStack == 16 ? kStack + kSteps : kStack;
+    // row 0 stays unused: an empty stack's top
+    __shared__ uint32_t lds_stack[(kRows + 1) * kTB];
     const uint32_t grab = tk.grab;
     const int tid = threadIdx.x, lane = tid & 63;
     const uint32_t N = count_ptr ? *count_ptr : count;
     const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    uint32_t *stk = lds_stack + tid;
+    // LDS byte addresses: the lane's row 0 and its newest stack entry
+    const uint32_t stk = (uint32_t)(uintptr_t)(LdsWord *)(lds_stack + tid);
+    uint32_t top = stk;
 
-    bool active = false, exhausted = false;
     // rays [pool, pool_end) taken by this wave and not yet handed to a lane
     // (wave-uniform); a new batch of `grab` comes from the work counters only
     // when the pool is empty, so refills rarely touch an atomic
@@ -793,30 +843,114 @@ void k_traverse(SceneArgs S, Src src, uint32_t count, const uint32_t *count_ptr,
     bool drained = false;   // every work counter has passed N (wave-uniform)
     uint32_t part = blockIdx.x % kWorkParts;   // the work counter this wave takes from first
     uint32_t item = 0, node = 0;
-    int sp = 0;             // entries on the LDS stack
-    bool dropped = false;   // entries of this ray were dropped (found again through parent links)
-    float o[3], d[3];
     WRay wr;
     Hit h;
-    uint32_t visits = 0, tests = 0, drops = 0;
-    // pending leaf hits of this lane (tested when enough lanes have some)
+    uint32_t visits = 0, tests = 0;
+    // leaf hits of this lane not yet tested (tested when enough lanes have some)
     uint32_t q0 = 0, q1 = 0, q2 = 0, q3 = 0;
-    int nq = 0;
-    bool trav = false;   // the lane still has an inner node to visit
+    // The lane's state in one word, so that "may visit a node" is one
+    // comparison (state <= 2): how many leaf hits wait, + kNoNode when it has
+    // no inner node left to visit, kNoRay when it has no ray.
+    constexpr uint32_t kNoNode = 8, kNoRay = 16;
+    uint32_t state = kNoRay;
     SceneArgs Sl = S;    // scene of the lane's ray (differs per lane in a batch)
     int job = 0;         // job of the lane's ray (batches)
     if constexpr (Src::kPerLaneScene) src.init();
 
+    // One node visit: both children's slab tests, leaf hits to the queue, the
+    // next node.  The lane's stack runs from the row after `bottom` to `top`
+    // and has room for one more.  Written for few vector instructions, which
+    // bound the kernel: predicates are lane masks combined on the scalar unit,
+    // a push and a pop are each one masked add and one LDS access, and the
+    // second leaf of a node with two leaf hits is queued behind a branch that
+    // most waves skip.
+    auto visit = [&](float limit, uint32_t bottom) __attribute__((always_inline)) {
+        BvhNode16 nd;
+        if constexpr (Src::kPerLaneScene || kFar) nd = Sl.nodes[node];
+        else nd = *reinterpret_cast<const BvhNode16 *>(reinterpret_cast<const char *>(Sl.nodes) + (node << 5));
+        if constexpr (Src::kStats) ++visits;
+        float tl, tr;
+        bool hl, hr;
+        node_hits(wr, nd, limit, hl, hr, tl, tr);
+        const uint32_t L = nd.b.z, R = nd.b.w;
+        const uint64_t mhl = __ballot(hl), mhr = __ballot(hr);
+        const uint64_t mll = __ballot((int32_t)L < 0), mlr = __ballot((int32_t)R < 0);
+        const uint64_t mpl = mhl & mll, mpr = mhr & mlr, mil = mhl & ~mll, mir = mhr & ~mlr;
+        // a leaf hit goes to the front of the queue (shift in)
+        const bool pl = lanes(mpl), pa = lanes(mpl | mpr);
+        q3 = pa ? q2 : q3; q2 = pa ? q1 : q2; q1 = pa ? q0 : q1; q0 = pa ? (pl ? L : R) : q0;
+        state += pa ? 1u : 0u;
+        if ((mpl & mpr) != 0ull) {
+            const bool two = lanes(mpl & mpr);
+            q3 = two ? q2 : q3; q2 = two ? q1 : q2; q1 = two ? q0 : q1; q0 = two ? R : q0;
+            state += two ? 1u : 0u;
+        }
+        // next node: the near child when both are hit (the far one pushed),
+        // else the one hit child, else the stack top; a lane with none of
+        // these ends on its last node's right child
+        const bool left = lanes(mil & (__ballot(tl <= tr) | ~mir));
+        uint32_t next = left ? L : R, t = top;
+        if (lanes(mil & mir)) {
+            t += kRow;
+            *lds_word(t) = left ? R : L;
+        }
+        const uint64_t none = ~(mil | mir) & __ballot(true), pop = none & __ballot(t != bottom);
+        if (lanes(pop)) {
+            next = *lds_word(t);
+            t -= kRow;
+        }
+        node = next;
+        top = t;
+        state += lanes(none & ~pop) ? kNoNode : 0u;
+    };
+    // The oldest kDropChunk entries of a lane's stack go.
+    auto drop = [&]() __attribute__((always_inline)) {
+        for (uint32_t a = stk + kRow; a + kDropChunk * kRow <= top; a += kRow) *lds_word(a) = *lds_word(a + kDropChunk * kRow);
+        top -= kDropChunk * kRow;
+        wr.swx |= kDropped;
+        if (Src::kStats && drops_out) atomicAdd(drops_out + (blockIdx.x % kWorkParts) * kWorkStride, 1u);
+    };
+    // A lane whose stack ran empty after a drop: up from its finished subtree
+    // to the nearest ancestor whose far child is still pending.
+    auto walk = [&](float limit) __attribute__((always_inline)) {
+        uint32_t c = Sl.parent[(node & kLeaf) ? (size_t)(Sl.nleaf - 1) + (node & ~kLeaf) : (size_t)node];
+        wr.swx &= ~kDropped;
+        for (uint32_t a = Sl.parent[c]; a != ~0u; c = a, a = Sl.parent[a]) {
+            const BvhNode16 pn = Sl.nodes[a];
+            if constexpr (Src::kStats) ++visits;
+            float ta, tb;
+            bool ha, hb;
+            node_hits(wr, pn, limit, ha, hb, ta, tb);
+            const bool from_left = pn.b.z == c;
+            const uint32_t other = from_left ? pn.b.w : pn.b.z;
+            const bool came_near = from_left ? ta <= tb : !(ta <= tb);
+            if (came_near && (other & kLeaf) == 0u && (from_left ? hb : ha)) {
+                node = other;
+                state -= kNoNode;
+                wr.swx |= kDropped;
+                break;
+            }
+        }
+    };
+
+    // A launch with no more rays than lanes deals them evenly over its waves,
+    // without counters; a larger one hands them out in runs.
+    if (N <= gridDim.x * (uint32_t)kTB) {
+        const uint32_t wave = blockIdx.x * (kTB / 64) + (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6), waves = gridDim.x * (kTB / 64);
+        pool = (uint32_t)((uint64_t)N * wave / waves);
+        pool_end = (uint32_t)((uint64_t)N * (wave + 1) / waves);
+        drained = true;
+    }
     while (true) {
-        const uint64_t idle = __ballot(!active && !exhausted);
-        const uint64_t live = __ballot(active);
-        if (idle != 0ull && (__popcll(idle) >= tk.refill || live == 0ull)) {
-            if (pool == pool_end && !drained) {
+        const uint64_t idle = __ballot(state >= kNoRay);
+        if (!(drained && pool == pool_end) && (__popcll(idle) >= tk.refill || idle == ~0ull) && idle != 0ull) {
+            if (pool == pool_end) {
                 // chunk g = k * kWorkParts + part is the k-th take of counter
                 // part; a counter past the last chunk sends the wave on to
                 // the next, and a wave that finds all past it is drained
                 uint32_t base = N;
                 if (lane == 0) {
+#pragma unroll 1
                     for (int t = 0; t < kWorkParts; ++t) {
                         const uint32_t k = atomicAdd(work + part * kWorkStride, 1u);
                         const uint64_t b = ((uint64_t)k * kWorkParts + part) * grab;
@@ -827,8 +961,8 @@ void k_traverse(SceneArgs S, Src src, uint32_t count, const uint32_t *count_ptr,
                         part = part + 1 == kWorkParts ? 0u : part + 1;
                     }
                 }
-                base = __shfl(base, 0);
-                part = __shfl(part, 0);
+                base = __builtin_amdgcn_readfirstlane(base);
+                part = __builtin_amdgcn_readfirstlane(part);
                 if (base >= N) {
                     drained = true;
                 } else {
@@ -838,136 +972,181 @@ void k_traverse(SceneArgs S, Src src, uint32_t count, const uint32_t *count_ptr,
             }
             const uint32_t avail = pool_end - pool;
             const uint32_t rank = (uint32_t)__popcll(idle & lt);
-            if (!active && !exhausted) {
+            if (state >= kNoRay && rank < avail) {
                 item = pool + rank;
-                if (rank < avail) {
-                    if (tk.reverse) item = N - 1u - item;   // pool + rank < N
-                    if constexpr (Src::kPerLaneScene) {
-                        job = src.job_of(item);
-                        Sl = src.scene(job);
-                        src.start(item, job, o, d, wr);
-                    } else {
-                        src.start(item, o, d, wr);
-                    }
-                    h = Hit{INFINITY, ~0u, 0u};
-                    node = 0;
-                    sp = 0;
-                    dropped = false;
-                    nq = 0;
-                    active = true;
-                    if (Sl.nleaf == 1) {
-                        trav = false;
-                        q0 = 0u;
-                        nq = 1;
-                    } else {
-                        trav = true;
-                    }
-                } else if (drained) {
-                    exhausted = true;
+                if (tk.reverse) item = N - 1u - item;   // pool + rank < N
+                if constexpr (Src::kPerLaneScene) {
+                    job = src.job_of(item);
+                    Sl = src.scene(job);
+                    src.start(item, job, wr);
+                } else {
+                    src.start(item, wr);
+                }
+                h = Hit{INFINITY, ~0u, 0u};
+                node = 0;
+                top = stk;
+                state = 0;
+                if (Sl.nleaf == 1) {   // the only leaf
+                    state = kNoNode + 1;
+                    q0 = 0u;
                 }
             }
             const uint32_t nidle = (uint32_t)__popcll(idle);
             pool += nidle < avail ? nidle : avail;
         }
-        if (__ballot(active) == 0ull) {
-            if (__ballot(!exhausted) == 0ull) break;
-            continue;
-        }
+        const uint64_t busy = __ballot(state < kNoRay);
+        if (drained && pool == pool_end && __popcll(busy) <= (tk.leaf_batch > 1 ? kShareLanes : 0)) break;
+        if (busy == 0ull) continue;
         // triangle tests, batched across the wave
-        const bool want = active && nq > 0;
-        const bool must = want && (nq >= 3 || !trav);
-        if (__ballot(must) != 0ull || __popcll(__ballot(want)) >= tk.leaf_batch) {
+        const bool want = (state & 7u) != 0u;
+        if (__ballot(want && state >= 3u) != 0ull || __popcll(__ballot(want)) >= tk.leaf_batch) {
             if (want) {
-                ++tests;
-                consider_leaf(Sl, wr, q0, h);
+                if constexpr (Src::kStats) ++tests;
+                consider_leaf(Sl, wr, q0 & ~kLeaf, h);
                 q0 = q1; q1 = q2; q2 = q3;
-                --nq;
+                --state;
             }
         }
+        // prune against the best hit, 2^-10 relative slack
+        const float limit = h.t * 1.0009765625f;
+        if (top > stk + (kRows - kSteps) * kRow) drop();
 #pragma unroll
-        for (int step = 0; step < kSteps; ++step) {
-            if (!(active && trav && nq <= 2)) continue;
-            const uint32_t nd_self = node;
-            const BvhNode16 nd = Sl.nodes[node];
-            ++visits;
-            const float limit = h.t * 1.0009765625f;   // prune against the best hit, 2^-10 relative slack
-            float tl, tr;
-            bool hl, hr;
-            node_hits(wr, nd, limit, hl, hr, tl, tr);
-            const uint32_t L = nd.b.z, R = nd.b.w;
-            // leaf children go to the front of the pending queue (shift in)
-            const bool pl = hl && (L & kLeaf) != 0u, pr = hr && (R & kLeaf) != 0u;
-            q3 = pl ? q2 : q3; q2 = pl ? q1 : q2; q1 = pl ? q0 : q1; q0 = pl ? (L & ~kLeaf) : q0;
-            q3 = pr ? q2 : q3; q2 = pr ? q1 : q2; q1 = pr ? q0 : q1; q0 = pr ? (R & ~kLeaf) : q0;
-            nq += (int)pl + (int)pr;
-            hl = hl && !pl;
-            hr = hr && !pr;
-            const bool both = hl && hr;
-            const bool none = !hl && !hr;
-            if (both && sp == kStack) {
-                // stack full: the oldest entries go (the parent walk finds them again)
-                for (int i = 0; i < kStack - kDropChunk; ++i) stk[i * kTB] = stk[(i + kDropChunk) * kTB];
-                sp -= kDropChunk;
-                dropped = true;
-                ++drops;
-            }
-            // next node by selects (no divergent branches): the near child when both are
-            // hit (the far one pushed), else the one hit child, else the stack top
-            const bool nearl = tl <= tr;
-            if (both) stk[sp * kTB] = nearl ? R : L;
-            const bool pop = none && sp > 0;
-            uint32_t top = 0u;
-            if (pop) top = stk[(sp - 1) * kTB];
-            const uint32_t one = hl ? L : R;
-            node = both ? (nearl ? L : R) : (none ? top : one);
-            sp += both ? 1 : (pop ? -1 : 0);
-            if (none && !pop) {
-                trav = false;
-                if (dropped) {
-                    // stack empty after a drop: walk up from this finished subtree
-                    // to the nearest ancestor whose far child is still pending
-                    uint32_t c = nd_self;
-                    for (uint32_t a = Sl.parent[c]; a != ~0u; c = a, a = Sl.parent[a]) {
-                        const BvhNode16 pn = Sl.nodes[a];
-                        ++visits;
-                        const float lim = h.t * 1.0009765625f;
-                        float ta, tb;
-                        bool ha, hb;
-                        node_hits(wr, pn, lim, ha, hb, ta, tb);
-                        const bool from_left = pn.b.z == c;
-                        const uint32_t other = from_left ? pn.b.w : pn.b.z;
-                        const bool came_near = from_left ? ta <= tb : !(ta <= tb);
-                        if (came_near && (other & kLeaf) == 0u && (from_left ? hb : ha)) {
-                            node = other;
-                            trav = true;
-                            break;
-                        }
-                    }
-                }
-            }
-        }
-        if (active && !trav && nq == 0) {
-            if constexpr (Src::kPerLaneScene) src.finish(Sl, item, job, o, d, h);
-            else src.finish(Sl, item, o, d, h);
-            active = false;
+        for (int step = 0; step < kSteps; ++step)
+            if (state <= 2u) visit(limit, stk);
+        if (state >= kNoNode && state < kNoRay && (int32_t)wr.swx < 0) walk(limit);
+        if (state == kNoNode) {
+            if constexpr (Src::kPerLaneScene) src.finish(item, job, h);
+            else src.finish(item, h);
+            state = kNoRay;
+            top = stk;
         }
     }
-    if (stats) {
+
+    // Work sharing: no ray is left to hand out and at most kShareLanes lanes
+    // of the wave still have one.  An idle lane takes the oldest stack entry
+    // (the largest pending subtree) of a busy one, with its ray, and both go
+    // on; a ray's best hit, the lanes at work on it and its hit's leaf live in
+    // LDS under the lane that owns it, and the owner finishes the ray when the
+    // last of them is through.  The closest hit does not depend on the order
+    // of the visits, so neither does any result.  The last rows of the wave's
+    // own stack columns hold that state.  A lane that drops entries walks on
+    // past the subtree it was given, over work that others do too, and gives
+    // none away itself.  With trace_leaf_batch 1 every ray stays with its lane,
+    // so that the statistics follow from the rays alone.
+    // 1000 rays among 866 triangles took 102 us, a node visit after the other
+    // with 64 rays to a wave, and take 20; a 256 x 256 view's rays 103 and 31.
+    if (__ballot(state < kNoRay) != 0ull) {
+        constexpr int kTop = kRows - kShareRows;   // rows left to the stack
+        static_assert(kRows - kDropChunk <= kTop && kDropChunk + kShareSteps <= kTop, "room for the shared state");
+        const int wb = tid & ~63;   // the wave's first column
+        auto key_of = [&](int l) __attribute__((always_inline)) {
+            return reinterpret_cast<unsigned long long *>(lds_stack + (1 + kTop + (l >> 5)) * kTB + wb + 2 * (l & 31));
+        };
+        uint32_t *s_leaf = lds_stack + (kTop + 3) * kTB + wb, *s_work = lds_stack + (kTop + 4) * kTB + wb;
+        uint32_t *s_from = lds_stack + (kTop + 5) * kTB + wb, *s_node = lds_stack + (kTop + 6) * kTB + wb;
+        if (top > stk + kTop * kRow) drop();
+        wave_sync();
+        bool mine = state < kNoRay;   // the lane's own ray is unfinished
+        *key_of(lane) = ((unsigned long long)__float_as_uint(h.t) << 32) | h.id;
+        s_leaf[lane] = h.leaf;
+        s_work[lane] = mine ? 1u : 0u;
+        int owner = lane;
+        uint32_t bottom = stk;   // the stack's first entry lies above; the rows below it were given away
+        wave_sync();
+        while (true) {
+            const uint64_t live = __ballot(state < kNoRay);
+            if (live == 0ull) break;
+            const bool can = state < kNoNode && top != bottom && (int32_t)wr.swx >= 0;
+            const uint64_t donors = __ballot(can);
+            if (donors != 0ull && live != ~0ull) {
+                const int give = __popcll(donors & lt), take = __popcll(~live & lt);
+                const int n = min(__popcll(donors), __popcll(~live));
+                if (can && give < n) {
+                    bottom += kRow;
+                    s_from[give] = (uint32_t)lane;
+                    s_node[give] = *lds_word(bottom);
+                }
+                wave_sync();
+                const bool taker = state >= kNoRay && take < n;
+                const int from = taker ? (int)s_from[take] : lane;
+                const uint32_t first = taker ? s_node[take] : node;
+                wave_sync();
+                wr.o0 = __shfl(wr.o0, from); wr.o1 = __shfl(wr.o1, from); wr.o2 = __shfl(wr.o2, from);
+                wr.sx = __shfl(wr.sx, from); wr.sy = __shfl(wr.sy, from); wr.sz = __shfl(wr.sz, from);
+                wr.ix = __shfl(wr.ix, from); wr.iy = __shfl(wr.iy, from); wr.iz = __shfl(wr.iz, from);
+                wr.cnx = __shfl(wr.cnx, from); wr.cny = __shfl(wr.cny, from); wr.cnz = __shfl(wr.cnz, from);
+                wr.cfx = __shfl(wr.cfx, from); wr.cfy = __shfl(wr.cfy, from); wr.cfz = __shfl(wr.cfz, from);
+                wr.swx = __shfl(wr.swx, from); wr.swy = __shfl(wr.swy, from); wr.swz = __shfl(wr.swz, from);
+                owner = __shfl(owner, from);
+                if constexpr (Src::kPerLaneScene) {
+                    const int oj = __shfl(job, owner);
+                    if (taker) Sl = src.scene(oj);
+                }
+                if (taker) {
+                    node = first;
+                    top = stk;
+                    bottom = stk;
+                    state = 0;
+                    atomicAdd(&s_work[owner], 1u);
+                }
+            }
+            const bool want = (state & 7u) != 0u;
+            if (__ballot(want && state >= 3u) != 0ull || 2 * __popcll(__ballot(want)) >= __popcll(live)) {
+                if (want) {
+                    if constexpr (Src::kStats) ++tests;
+                    unsigned long long *best = key_of(owner);
+                    Hit g{__uint_as_float((uint32_t)(*best >> 32)), (uint32_t)*best, ~0u};
+                    consider_leaf(Sl, wr, q0 & ~kLeaf, g);
+                    const unsigned long long key = ((unsigned long long)__float_as_uint(g.t) << 32) | g.id;
+                    if (g.leaf != ~0u) atomicMin(best, key);
+                    wave_sync();
+                    // of lanes that improve one ray together, the closest names the leaf
+                    if (g.leaf != ~0u && *best == key) s_leaf[owner] = g.leaf;
+                    q0 = q1; q1 = q2; q2 = q3;
+                    --state;
+                }
+            }
+            wave_sync();
+            const float limit = __uint_as_float((uint32_t)(*key_of(owner) >> 32)) * 1.0009765625f;
+            // room for kShareSteps pushes: the stack moves down over the rows
+            // given away, and drops entries where those are too few
+            constexpr uint32_t most = (kTop - kShareSteps) * kRow;
+            if (top > stk + most && bottom != stk) {
+                const uint32_t d = bottom - stk;
+                for (uint32_t a = stk + kRow; a + d <= top; a += kRow) *lds_word(a) = *lds_word(a + d);
+                top -= d;
+                bottom = stk;
+            }
+            if (top > stk + most) drop();
+#pragma unroll 1
+            for (int step = 0; step < kShareSteps; ++step)
+                if (state <= 2u) visit(limit, bottom);
+            if (state >= kNoNode && state < kNoRay && (int32_t)wr.swx < 0) walk(limit);
+            if (state == kNoNode) {
+                state = kNoRay;
+                atomicSub(&s_work[owner], 1u);
+            }
+            wave_sync();
+            if (mine && s_work[lane] == 0u) {
+                const unsigned long long key = *key_of(lane);
+                h = Hit{__uint_as_float((uint32_t)(key >> 32)), (uint32_t)key, s_leaf[lane]};
+                if constexpr (Src::kPerLaneScene) src.finish(item, job, h);
+                else src.finish(item, h);
+                mine = false;
+            }
+        }
+    }
+    if (Src::kStats && stats) {
         unsigned long long v = visits, t = tests;
         for (int off = 32; off >= 1; off >>= 1) {
             v += __shfl_xor(v, off);
             t += __shfl_xor(t, off);
         }
-        if (lane == 0) {
+        if (lane == 0 && v) {
             unsigned long long *slot = stats + (blockIdx.x % kWorkParts) * (kWorkStride / 2);
             atomicAdd(slot, v);
             atomicAdd(slot + 1, t);
         }
-    }
-    if (drops_out) {
-        uint32_t sv = drops;
-        for (int off = 32; off >= 1; off >>= 1) sv += __shfl_xor(sv, off);
-        if (lane == 0 && sv) atomicAdd(drops_out + (blockIdx.x % kWorkParts) * kWorkStride, sv);
     }
 }
 
@@ -1006,16 +1185,42 @@ int clamp_blocks(int blocks) { return blocks < 1 ? 1 : (blocks > kMaxTraceBlocks
 template <class Src, int kStack, class F>
 void with_steps(int steps, F f)
 {
-    if (steps == 3) f(k_traverse<Src, kStack, 3>);
-    else f(k_traverse<Src, kStack, 4>);
+    if (steps == 3) f(k_traverse<Src, kStack, 3, false>);
+    else f(k_traverse<Src, kStack, 4, false>);
 }
 
+// Trees of up to kMaxNear leaves keep a node's byte offset in 32 bits (one
+// shift per visit in place of 64-bit address arithmetic); a larger one runs
+// the default shape's 64-bit variant.
+constexpr int32_t kMaxNear = 1 << 27;
+
 template <class Src, class F>
-void with_shape(int stack, int steps, F f)
+void with_shape(int stack, int steps, int32_t nleaf, F f)
 {
-    if (stack == 16) with_steps<Src, 16>(steps, f);
+    if (!Src::kPerLaneScene && nleaf > kMaxNear) f(k_traverse<Src, kStackLds, kTraceSteps, !Src::kPerLaneScene>);
+    else if (stack == 16) with_steps<Src, 16>(steps, f);
     else if (stack == 32) with_steps<Src, 32>(steps, f);
     else with_steps<Src, kStackLds>(steps, f);
+}
+
+// The sources without launch knobs run the default shape.
+template <class Src, class F>
+void with_default(int32_t nleaf, F f)
+{
+    if (nleaf > kMaxNear) f(k_traverse<Src, kStackLds, kTraceSteps, true>);
+    else f(k_traverse<Src, kStackLds, kTraceSteps, false>);
+}
+
+// A traversal of few rays needs no more blocks than give each wave kMinRays
+// of them: they spread over the chip, and work sharing spreads each over its
+// wave (1000 rays: 21.1, 21.2, 22.0, 22.9 us at 1, 2, 4, 8 rays per wave, but
+// a 256 x 256 view is no slower at 16, so the line saves launching blocks).
+constexpr int kMinRays = 4;
+
+int blocks_for(int blocks, int64_t rays)
+{
+    const int64_t per = (int64_t)kMinRays * (kTB / 64), need = (rays + per - 1) / per;
+    return need < blocks ? (need < 1 ? 1 : (int)need) : blocks;
 }
 
 int trace_blocks_per_cu(bool batch, int stack, int steps)
@@ -1023,8 +1228,8 @@ int trace_blocks_per_cu(bool batch, int stack, int steps)
     int n = 0;
     hipError_t e = hipSuccess;
     auto occ = [&](auto kern) { e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kern, kTB, 0); };
-    if (batch) with_shape<BatchRays>(stack, steps, occ);
-    else with_shape<LensRays>(stack, steps, occ);
+    if (batch) with_shape<BatchRays>(stack, steps, 0, occ);
+    else with_shape<LensRays>(stack, steps, 0, occ);
     return e == hipSuccess ? n : 0;
 }
 
@@ -1037,7 +1242,7 @@ hipError_t launch_trace(const SceneDev &s, const FrameConst &fc, const ScratchLa
     src.rec1 = P.rec1;
     src.ray_lt = P.ray_lt;
     uint32_t *cnt = reinterpret_cast<uint32_t *>(scratch + L.counters);
-    with_shape<LensRays>(fc.tk.stack, fc.tk.steps, [&](auto kern) {
+    with_shape<LensRays>(fc.tk.stack, fc.tk.steps, s.nleaf, [&](auto kern) {
         kern<<<clamp_blocks(blocks), kTB, 0, st>>>(scene_args(s), src, 0u, cnt + kCntRays, cnt + kCntWork,
                                                   reinterpret_cast<unsigned long long *>(cnt + kCntWork + kStatAt),
                                                   cnt + kCntWork + kStatAt + 4, fc.tk);
@@ -1076,17 +1281,14 @@ hipError_t launch_shade_resolve(const SceneDev &s, const FrameConst &fc, const S
 hipError_t launch_gbuffer(const SceneDev &s, const FrameConst &fc, void *colour, int cfmt, float *depth, void *normal,
                           int nfmt, int blocks, hipStream_t st)
 {
-    PinholeRays src;
-    src.fc = fc;
-    src.shade = fc.shade;
-    src.colour = colour;
-    src.cfmt = cfmt;
-    src.depth = depth;
-    src.normal = normal;
-    src.nfmt = nfmt;
-    k_zero_work<<<1, 64, 0, st>>>(s.aux);
-    k_traverse<PinholeRays, kStackLds, kTraceSteps><<<clamp_blocks(blocks), kTB, 0, st>>>(
-        scene_args(s), src, (uint32_t)((int64_t)fc.W * fc.H), nullptr, s.aux, nullptr, nullptr, fc.tk);
+    const PinholeRays src{fc.cur, fc.W, fc.H, depth, static_cast<uint32_t *>(normal), nfmt == DOF_RGBA32F ? 4u : 2u};
+    const int64_t rays = (int64_t)fc.W * fc.H;
+    blocks = blocks_for(clamp_blocks(blocks), rays);
+    if (rays > (int64_t)blocks * kTB) k_zero_work<<<1, 64, 0, st>>>(s.aux);   // fewer are dealt without counters
+    with_default<PinholeRays>(s.nleaf, [&](auto kern) {
+        kern<<<blocks, kTB, 0, st>>>(scene_args(s), src, (uint32_t)rays, nullptr, s.aux, nullptr, nullptr, fc.tk);
+    });
+    k_gbuffer_shade<<<(unsigned)((rays + 255) / 256), 256, 0, st>>>(scene_args(s), fc.shade, src, colour, cfmt, nfmt, (uint32_t)rays);
     return hipGetLastError();
 }
 
@@ -1095,10 +1297,12 @@ hipError_t launch_trace_rays(const SceneDev &s, int64_t n, const float *org, con
 {
     if (n == 0) return hipSuccess;
     RawRays src{org, dir, hit, t};
-    k_zero_work<<<1, 64, 0, st>>>(s.aux);
+    blocks = blocks_for(clamp_blocks(blocks), n);
+    if (n > (int64_t)blocks * kTB) k_zero_work<<<1, 64, 0, st>>>(s.aux);
     TraceKnobs tk{kStackLds, 64u, 16, 32};
-    k_traverse<RawRays, kStackLds, kTraceSteps><<<clamp_blocks(blocks), kTB, 0, st>>>(scene_args(s), src, (uint32_t)n, nullptr, s.aux,
-                                                                         nullptr, nullptr, tk);
+    with_default<RawRays>(s.nleaf, [&](auto kern) {
+        kern<<<blocks, kTB, 0, st>>>(scene_args(s), src, (uint32_t)n, nullptr, s.aux, nullptr, nullptr, tk);
+    });
     return hipGetLastError();
 }
 
@@ -1110,8 +1314,10 @@ hipError_t launch_reference(const SceneDev &s, const FrameConst &fc, int spp, ui
         const uint32_t n = (uint32_t)(npx - p0 < chunk_px ? npx - p0 : chunk_px);
         RefRays src{fc, (uint32_t)p0, (uint32_t)spp, lt};
         k_zero_work<<<1, 64, 0, st>>>(s.aux);
-        k_traverse<RefRays, kStackLds, kTraceSteps><<<clamp_blocks(blocks), kTB, 0, st>>>(scene_args(s), src, n * (uint32_t)spp,
-                                                                            nullptr, s.aux, nullptr, nullptr, fc.tk);
+        with_default<RefRays>(s.nleaf, [&](auto kern) {
+            kern<<<clamp_blocks(blocks), kTB, 0, st>>>(scene_args(s), src, n * (uint32_t)spp, nullptr, s.aux, nullptr,
+                                                       nullptr, fc.tk);
+        });
         k_ref_average<<<(n + 255) / 256, 256, 0, st>>>(scene_args(s), src, n, colour, cfmt);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -1130,7 +1336,7 @@ hipError_t launch_batch_trace(BatchHead *head, const Job *jobs, int njobs, int b
                               hipStream_t st)
 {
     BatchRays src{jobs, head, njobs};
-    with_shape<BatchRays>(tk.stack, tk.steps, [&](auto kern) {
+    with_shape<BatchRays>(tk.stack, tk.steps, 0, [&](auto kern) {
         kern<<<clamp_blocks(blocks), kTB, 0, st>>>(SceneArgs{}, src, 0u, &head->rays, head->work,
                                                   reinterpret_cast<unsigned long long *>(head->work + kStatAt),
                                                   nullptr, tk);
