@@ -64,10 +64,10 @@ constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 
 struct SceneLayout {
-    size_t verts_in, albedo_in, ref_off, ref_box, ref_tri, tris, albedo, nodes, nodes16, parent, keys, keys_tmp, ids,
+    size_t verts_in, albedo_in, ref_off, refs, tris, albedo, nodes, nodes16, parent, keys, keys_tmp, ids,
         ids_tmp;
-    size_t flags, hist, bounds, aux, total;
-    int sort_blocks, bound_blocks;
+    size_t hist, bounds, aux, total;
+    int bound_blocks;
 };
 
 // nt triangles, n leaf references
@@ -81,25 +81,22 @@ SceneLayout scene_layout(int64_t nt, int64_t n)
         return o;
     };
     const int64_t ni = n > 1 ? n - 1 : 1;
-    L.sort_blocks = (int)((n + 4095) / 4096);
     L.bound_blocks = (int)std::min<int64_t>(1024, (n + 255) / 256);
     L.verts_in = take(sizeof(float) * 9 * nt);
     L.albedo_in = take(sizeof(float) * 3 * nt);
     L.ref_off = take(sizeof(uint32_t) * (nt + 1));
-    L.ref_box = take(sizeof(float) * 6 * n);
-    L.ref_tri = take(sizeof(uint32_t) * n);
+    L.refs = take(sizeof(dof::LeafRef) * n);
     L.tris = take(sizeof(float4) * 3 * n);
     L.albedo = take(sizeof(float4) * n);
     L.nodes = take(sizeof(dof::BvhNode) * ni);
     L.nodes16 = take(sizeof(dof::BvhNode16) * ni);
     L.parent = take(sizeof(uint32_t) * (2 * n - 1));
     L.keys = take(sizeof(uint64_t) * n);
-    L.keys_tmp = take(sizeof(uint64_t) * n);
+    L.keys_tmp = take((size_t)dof::keys_tmp_bytes(n));
     L.ids = take(sizeof(uint32_t) * n);
     L.ids_tmp = take(sizeof(uint32_t) * n);
-    L.flags = take(sizeof(uint32_t) * ni);
-    L.hist = take(sizeof(uint32_t) * 256 * ((size_t)L.sort_blocks + 1));
-    L.bounds = take(sizeof(float) * (6 * (size_t)L.bound_blocks + 8));
+    L.hist = take(sizeof(uint32_t) * (size_t)dof::sort_words(n));
+    L.bounds = take(sizeof(float) * 6 * (size_t)L.bound_blocks);
     L.aux = take(dof::kWorkBytes);
     L.total = off;
     return L;
@@ -666,8 +663,7 @@ dof_status dof_create_scene(const dof_scene_desc *desc, void *arena, size_t aren
     d.verts_in = reinterpret_cast<float *>(a + L.verts_in);
     d.albedo_in = reinterpret_cast<float *>(a + L.albedo_in);
     d.ref_off = reinterpret_cast<uint32_t *>(a + L.ref_off);
-    d.ref_box = reinterpret_cast<float *>(a + L.ref_box);
-    d.ref_tri = reinterpret_cast<uint32_t *>(a + L.ref_tri);
+    d.refs = reinterpret_cast<dof::LeafRef *>(a + L.refs);
     d.tris = reinterpret_cast<float4 *>(a + L.tris);
     d.albedo = reinterpret_cast<float4 *>(a + L.albedo);
     d.nodes = reinterpret_cast<dof::BvhNode *>(a + L.nodes);
@@ -677,11 +673,9 @@ dof_status dof_create_scene(const dof_scene_desc *desc, void *arena, size_t aren
     d.keys_tmp = reinterpret_cast<uint64_t *>(a + L.keys_tmp);
     d.ids = reinterpret_cast<uint32_t *>(a + L.ids);
     d.ids_tmp = reinterpret_cast<uint32_t *>(a + L.ids_tmp);
-    d.flags = reinterpret_cast<uint32_t *>(a + L.flags);
     d.hist = reinterpret_cast<uint32_t *>(a + L.hist);
     d.bounds = reinterpret_cast<float *>(a + L.bounds);
     d.aux = reinterpret_cast<uint32_t *>(a + L.aux);
-    d.sort_blocks = L.sort_blocks;
     d.bound_blocks = L.bound_blocks;
     memcpy(s->shade.light_dir, desc->light_dir, sizeof(desc->light_dir));
     memcpy(s->shade.light_rad, desc->light_rad, sizeof(desc->light_rad));

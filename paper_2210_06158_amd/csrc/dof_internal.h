@@ -48,6 +48,12 @@ struct SceneShade {
     float light_dir[3], light_rad[3], ambient[3], sky[3];
 };
 
+struct LeafRef {      // 32 B, so that a gathered one is one aligned access
+    float lo[3], hi[3];
+    uint32_t tri;     // its triangle
+    uint32_t pad;
+};
+
 // The tree's leaves are references: a triangle, or (early split clipping)
 // one of four pieces of a long thin triangle clipped to quarters of its box.
 struct SceneDev {
@@ -56,20 +62,17 @@ struct SceneDev {
     const float *verts_in;   // 9 per triangle, original order
     const float *albedo_in;  // 3 per triangle, original order
     const uint32_t *ref_off; // ntri + 1: triangle i owns references ref_off[i] .. ref_off[i+1]-1
-    float *ref_box;          // 6 per reference: lo xyz, hi xyz
-    uint32_t *ref_tri;       // triangle of each reference
+    LeafRef *refs;           // nleaf references
     float4 *tris;            // 3 per leaf, sorted order; tris[3i].w = triangle id bits
     float4 *albedo;          // 1 per leaf, sorted order
     BvhNode *nodes;          // nleaf - 1
     BvhNode16 *nodes16;      // nleaf - 1: the traversal's binary16 copy
     uint32_t *parent;        // 2 nleaf - 1
-    uint64_t *keys, *keys_tmp;   // 63-bit Morton codes
+    uint64_t *keys, *keys_tmp;   // 63-bit Morton codes; the second buffer of the sort, then the tree's exit lists
     uint32_t *ids, *ids_tmp;     // reference indices (sorted: in leaf order)
-    uint32_t *flags;         // nleaf - 1 refit visit counters
-    uint32_t *hist;          // radix histograms (digit-major) + 256 digit offsets
-    float *bounds;           // 6 partial-bound slots per reduce block + 8 final
-    uint32_t *aux;           // work counters of the scene-level traversal kernels ([8]: the refit's exit count)
-    int32_t sort_blocks;
+    uint32_t *hist;          // the sort's counts and look-back words, then the tree's exit counts
+    float *bounds;           // 6 partial bounds per block of references
+    uint32_t *aux;           // work counters of the scene-level traversal kernels
     int32_t bound_blocks;
 };
 
@@ -268,6 +271,8 @@ __device__ inline float coc_px(float cock, float d, float z) { return cock * fab
 dof_status set_error(dof_status code, const char *fmt, ...);
 
 // bvh.hip
+int64_t sort_words(int64_t n);       // u32 words of SceneDev::hist for n leaf references
+int64_t keys_tmp_bytes(int64_t n);   // bytes of SceneDev::keys_tmp
 hipError_t launch_build_bvh(SceneDev &s, hipStream_t st);
 
 // trace.hip
