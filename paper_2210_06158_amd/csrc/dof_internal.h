@@ -242,9 +242,10 @@ inline size_t batch_table_bytes(int n)
     return (sizeof(BatchHead) + 255) / 256 * 256 + sizeof(Job) * (size_t)n;
 }
 
-// counters[] (u32) in scratch: [0] masked px, [1] rays; from [64] (256 B in)
+// counters[] (u32) in scratch: [0] masked px, [1] rays, [2] nonzero when the
+// temporal stage met a colour that the reconstruction may not weigh by 0; from [64] (256 B in)
 // the traversal's work-counter and statistics slots
-enum : int { kCntMasked = 0, kCntRays = 1, kCntWork = 64 };
+enum : int { kCntMasked = 0, kCntRays = 1, kCntWild = 2, kCntWork = 64 };
 constexpr size_t kCountersBytes = sizeof(uint32_t) * kCntWork + kWorkBytes;
 
 // ---------------------------------------------------------------- helpers

@@ -763,6 +763,7 @@ __global__ __launch_bounds__(256) void k_compact_count(int64_t np, const uint8_t
         uint32_t *w = P.counters + kCntWork + threadIdx.x * kWorkStride;
         w[0] = 0u;
         for (int k = 0; k < kStatWords; ++k) w[kStatAt + k] = 0u;
+        if (threadIdx.x == 0) P.counters[kCntWild] = 0u;
     }
     b_compact_count(np, mask, P, blockIdx.x, blockIdx.y);
 }
@@ -806,6 +807,7 @@ __device__ inline void b_compact_scan(int64_t nchunks, const Planes &P)
     if (threadIdx.x == 1023) {
         P.counters[kCntMasked] = pp[1023];
         P.counters[kCntRays] = pr[1023];
+        P.counters[kCntWild] = 0u;
     }
 }
 
@@ -906,6 +908,10 @@ __global__ __launch_bounds__(256) void kb_compact_scatter(const Job *__restrict_
 
 // ---------------------------------------------------------------- A12
 
+// A frame with a ray-traced colour beyond this (or none at all: NaN) is
+// marked "wild": sums over its taps might not be finite.
+constexpr float kTameColour = 1e18f;
+
 __device__ inline void b_temporal(const FrameConst &fc, const Planes &P, const uint8_t *__restrict__ mask,
                                                        const void *hist_in, void *hist_out, const uint32_t bx, const uint32_t by)
 {
@@ -982,6 +988,11 @@ __device__ inline void b_temporal(const FrameConst &fc, const Planes &P, const u
     float v = mu2 - mu1 * mu1;
     v = v > 0.0f ? v : 0.0f;
     float age = vn ? hNb.w + 1.0f : 1.0f;
+    // what lets the reconstruction skip pixels whose blend weight is 0 (every
+    // lane stores the same value)
+    if (!(fmaxf(fmaxf(fabsf(crt[0]), fabsf(crt[1])), fabsf(crt[2])) <= kTameColour) || crt[0] != crt[0] || crt[1] != crt[1] ||
+        crt[2] != crt[2])
+        P.counters[kCntWild] = 1u;
     P.T0[i] = make_float4(crt[0], crt[1], crt[2], 1.0f);
     P.T1[i] = make_float4(ct, huse, v, 0.0f);
     ho.A[i] = make_float4(accN[0], accN[1], accN[2], accH);
@@ -1127,120 +1138,119 @@ __device__ inline bool mip_taps_inside(int c, float R, float sc, int n)
     return (lo + 0.5f) * sc - 0.5f >= 0.0f && (hi + 0.5f) * sc - 0.5f < (float)(n - 1);
 }
 
-// Trilinear accumulation of one tap: the two mip levels' bilinear samples
-// blended by the lod fraction, folded into eight texel weights (level 0
-// scaled by f0 = 1 - fl, level 1 by f1 = fl, both 0 for a rejected tap) and
-// summed with fused multiply-adds into the four channels.  Equal to the
-// per-tap lerp of two bilinear lerps in exact arithmetic (the
-// reconstruction's tolerance parity covers the rounding); which texels a tap
-// reads, and whether it counts, are decided exactly as in the per-pixel
-// definition.
-struct Tex4 {
-    float4 a, b, c, d;   // (x0, y0), (x1, y0), (x0, y1), (x1, y1)
+typedef float Texel __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) const Texel LdsTexel;
+
+// A mip level as a pixel's taps read it: from global memory, or (Lds) from
+// its box in LDS, whose texel (x, y) lies at LDS byte address
+// at + 16 x + row y.
+struct MipLevel {
+    float sc;                  // 2^-level
+    int w, h;                  // the level's size
+    const Texel *img;          // global
+    uint32_t at, row;          // LDS
+    int x0, x1, y0, y1;        // the box: first and last column and row
 };
 
-__device__ inline void acc_bilinear(const Tex4 &t, float fx, float fy, float f, float &a0, float &a1, float &a2,
-                                    float &a3)
+// Adds f times the bilinear sample at (x, y) of a level to the channel sums:
+// four texel weights applied with fused multiply-adds (equal to the nested
+// lerps in exact arithmetic; the reconstruction's tolerance parity covers the
+// rounding).  Inside: the caller has shown that no index needs a clamp.  From
+// LDS the clamp is into the box, which holds every index that the block's taps
+// reach after the clamp to the image, so it gives the same texels and every
+// LDS access stays inside the box.
+template <bool Inside, bool Lds>
+__device__ inline void acc_bilinear(const MipLevel &L, float x, float y, float f, float &a0, float &a1, float &a2, float &a3)
 {
-    const float wy1 = fy * f, wy0 = f - wy1;
-    const float wx0 = 1.0f - fx;
-    const float w00 = wx0 * wy0, w10 = fx * wy0, w01 = wx0 * wy1, w11 = fx * wy1;
-    a0 = fmaf(t.d.x, w11, fmaf(t.c.x, w01, fmaf(t.b.x, w10, fmaf(t.a.x, w00, a0))));
-    a1 = fmaf(t.d.y, w11, fmaf(t.c.y, w01, fmaf(t.b.y, w10, fmaf(t.a.y, w00, a1))));
-    a2 = fmaf(t.d.z, w11, fmaf(t.c.z, w01, fmaf(t.b.z, w10, fmaf(t.a.z, w00, a2))));
-    a3 = fmaf(t.d.w, w11, fmaf(t.c.w, w01, fmaf(t.b.w, w10, fmaf(t.a.w, w00, a3))));
-}
-
-// The four texels of a bilinear lookup at (x, y) of a w x h level: clamped to
-// the image, or (Inside) shown inside it by the caller.
-template <bool Inside>
-__device__ inline Tex4 fetch4(const float4 *img, int w, int h, float x, float y, float &fx, float &fy)
-{
-    Tex4 t;
+    float fx, fy;
+    Texel t00, t10, t01, t11;
     if (Inside) {
-        const int x0 = (int)x, y0 = (int)y;
+        const int xi = (int)x, yi = (int)y;
         fx = __builtin_amdgcn_fractf(x);
         fy = __builtin_amdgcn_fractf(y);
-        const float4 *r0 = img + (__mul24(y0, w) + x0), *r1 = r0 + w;
-        t.a = r0[0]; t.b = r0[1]; t.c = r1[0]; t.d = r1[1];
+        if (Lds) {
+            const uint32_t at = (uint32_t)(__mul24(yi, (int)L.row) + (int)(((uint32_t)xi << 4) + L.at));
+            const LdsTexel *r0 = (const LdsTexel *)(uintptr_t)at, *r1 = (const LdsTexel *)(uintptr_t)(at + L.row);
+            t00 = r0[0]; t10 = r0[1]; t01 = r1[0]; t11 = r1[1];
+        } else {
+            const Texel *r0 = L.img + (__mul24(yi, L.w) + xi), *r1 = r0 + L.w;
+            t00 = r0[0]; t10 = r0[1]; t01 = r1[0]; t11 = r1[1];
+        }
     } else {
         const float x0f = floorf(x), y0f = floorf(y);
         fx = x - x0f;
         fy = y - y0f;
         const int xi = (int)x0f, yi = (int)y0f;
-        const int xa = clampi(xi, 0, w - 1), xb = clampi(xi + 1, 0, w - 1);
-        const size_t ra = (size_t)clampi(yi, 0, h - 1) * w, rb = (size_t)clampi(yi + 1, 0, h - 1) * w;
-        t.a = img[ra + xa]; t.b = img[ra + xb]; t.c = img[rb + xa]; t.d = img[rb + xb];
+        const int xa = clampi(xi, L.x0, L.x1), xb = clampi(xi + 1, L.x0, L.x1);
+        const int ya = clampi(yi, L.y0, L.y1), yb = clampi(yi + 1, L.y0, L.y1);
+        if (Lds) {
+            const uint32_t ra = (uint32_t)__mul24(ya, (int)L.row) + L.at, rb = (uint32_t)__mul24(yb, (int)L.row) + L.at;
+            t00 = *(const LdsTexel *)(uintptr_t)(ra + 16u * (uint32_t)xa);
+            t10 = *(const LdsTexel *)(uintptr_t)(ra + 16u * (uint32_t)xb);
+            t01 = *(const LdsTexel *)(uintptr_t)(rb + 16u * (uint32_t)xa);
+            t11 = *(const LdsTexel *)(uintptr_t)(rb + 16u * (uint32_t)xb);
+        } else {
+            const size_t ra = (size_t)ya * L.w, rb = (size_t)yb * L.w;
+            t00 = L.img[ra + xa]; t10 = L.img[ra + xb]; t01 = L.img[rb + xa]; t11 = L.img[rb + xb];
+        }
     }
-    return t;
+    const float wy1 = fy * f, wy0 = f - wy1;
+    const float w11 = fx * wy1, w01 = wy1 - w11, w10 = fx * wy0, w00 = wy0 - w10;
+    a0 = fmaf(t11.x, w11, fmaf(t01.x, w01, fmaf(t10.x, w10, fmaf(t00.x, w00, a0))));
+    a1 = fmaf(t11.y, w11, fmaf(t01.y, w01, fmaf(t10.y, w10, fmaf(t00.y, w00, a1))));
+    a2 = fmaf(t11.z, w11, fmaf(t01.z, w01, fmaf(t10.z, w10, fmaf(t00.z, w00, a2))));
+    a3 = fmaf(t11.w, w11, fmaf(t01.w, w01, fmaf(t10.w, w10, fmaf(t00.w, w00, a3))));
 }
 
-// The same from a level staged in LDS: t holds its rows b[2]..b[3] and
-// columns b[0]..b[1], bw = b[1] - b[0] + 1 wide.  The box holds every index
-// the block's taps reach after the clamp to the image (see b_recon), so
-// clamping into the box gives the same texels as clamping into the image,
-// and every LDS access stays inside the staged box.
-template <bool Inside>
-__device__ inline Tex4 fetch4_lds(const float4 *tex, const int *b, int bw, float x, float y, float &fx, float &fy)
-{
-    Tex4 t;
-    if (Inside) {
-        const int x0 = (int)x, y0 = (int)y;
-        fx = __builtin_amdgcn_fractf(x);
-        fy = __builtin_amdgcn_fractf(y);
-        const float4 *r0 = tex + (__mul24(y0 - b[2], bw) + (x0 - b[0])), *r1 = r0 + bw;
-        t.a = r0[0]; t.b = r0[1]; t.c = r1[0]; t.d = r1[1];
-    } else {
-        const float x0f = floorf(x), y0f = floorf(y);
-        fx = x - x0f;
-        fy = y - y0f;
-        int x0 = (int)x0f, y0 = (int)y0f;
-        const int x1 = clampi(x0 + 1, b[0], b[1]) - b[0], y1 = clampi(y0 + 1, b[2], b[3]) - b[2];
-        x0 = clampi(x0, b[0], b[1]) - b[0];
-        y0 = clampi(y0, b[2], b[3]) - b[2];
-        const int r0 = y0 * bw, r1 = y1 * bw;
-        t.a = tex[r0 + x0]; t.b = tex[r0 + x1]; t.c = tex[r1 + x0]; t.d = tex[r1 + x1];
-    }
-    return t;
-}
+// The 81 taps of one pixel in tap order, the centre and then kReconTaps at a
+// time (every ring holds a multiple of eight taps at one distance).  Two at a
+// time keep the kernel at 4 waves per SIMD without spills: 3840x2160 takes
+// 2269 us a frame with two, 2295 with one or four and 2286 with eight (3 waves).  Which texels a tap reads, and whether it counts,
+// are decided exactly as in the per-pixel definition.  Every tap's fetches are
+// issued (indices in bounds: clamped, or shown inside) and rejected taps weigh
+// 0, so the loads of several taps can be in flight at once.  A tap counts when
+// its pixel is ray traced and its CoC radius reaches the tap (pixels that are
+// not carry -inf).  The scales are powers of two, so the fused coordinate maps
+// round as a product and a difference would.
+constexpr int kReconTaps = 2;
 
-// The 81 taps of one pixel in tap order, from global memory (Lds = false) or
-// from the staged levels.  Every tap's fetches are issued (indices in
-// bounds: clamped, or shown inside) and rejected taps weigh 0, so the loads
-// of several taps can be in flight at once.
 template <bool Inside, bool Lds>
-__device__ inline void recon_taps(int x, int y, float Rr, float fl, float sc0, float sc1, int hw, int hh,
-                                  const float4 *m0, int w0, int h0, const int *b0, const float4 *m1, int w1, int h1,
-                                  const int *b1, const Rings &rings, const float2 *tap, float &a0, float &a1,
-                                  float &a2, float &a3, float &sh, int &na)
+__device__ inline void recon_taps(int x, int y, float Rr, float fl, const MipLevel &L0, const MipLevel &L1, int hw, int hh,
+                                  const Rings &rings, const float2 *tap, float &a0, float &a1, float &a2, float &a3,
+                                  float &sh, int &na)
 {
-    const float omf = 1.0f - fl;
-#pragma unroll 3
-    for (int k = 0; k < kRingTaps; ++k) {
-        float dist = Rr * rings.frac[k];
-        float sx = (float)x + rings.ox[k] * Rr, sy = (float)y + rings.oy[k] * Rr;
-        size_t j;
-        if (Inside)
-            j = (uint32_t)(__umul24((int)(sy + 0.5f), hw) + (int)(sx + 0.5f));
-        else
-            j = (size_t)nearest_idx(sy, hh) * hw + nearest_idx(sx, hw);
-        // a tap counts when its pixel is ray traced and its CoC radius
-        // reaches the tap (invalid pixels carry -inf)
-        const float2 tj = tap[j];
-        const bool ok = tj.x * 0.25f >= dist;
-        const float u0 = (sx + 0.5f) * sc0 - 0.5f, v0 = (sy + 0.5f) * sc0 - 0.5f;
-        const float u1 = (sx + 0.5f) * sc1 - 0.5f, v1 = (sy + 0.5f) * sc1 - 0.5f;
-        float fx0, fy0, fx1, fy1;
-        const Tex4 t0 = Lds ? fetch4_lds<Inside>(m0, b0, w0, u0, v0, fx0, fy0) : fetch4<Inside>(m0, w0, h0, u0, v0, fx0, fy0);
-        const Tex4 t1 = Lds ? fetch4_lds<Inside>(m1, b1, w1, u1, v1, fx1, fy1) : fetch4<Inside>(m1, w1, h1, u1, v1, fx1, fy1);
-        acc_bilinear(t0, fx0, fy0, ok ? omf : 0.0f, a0, a1, a2, a3);
-        acc_bilinear(t1, fx1, fy1, ok ? fl : 0.0f, a0, a1, a2, a3);
+    const float omf = 1.0f - fl, xf = (float)x, yf = (float)y;
+    auto one = [&](float sx, float sy, float2 tj, float reach) __attribute__((always_inline)) {
+        const bool ok = tj.x >= reach;   // CoC diameter against four times the distance: a quarter of it is exact
+        const float cx = sx + 0.5f, cy = sy + 0.5f;
+        acc_bilinear<Inside, Lds>(L0, fmaf(cx, L0.sc, -0.5f), fmaf(cy, L0.sc, -0.5f), ok ? omf : 0.0f, a0, a1, a2, a3);
+        acc_bilinear<Inside, Lds>(L1, fmaf(cx, L1.sc, -0.5f), fmaf(cy, L1.sc, -0.5f), ok ? fl : 0.0f, a0, a1, a2, a3);
         sh = sh + (ok ? tj.y : 0.0f);
         na += ok ? 1 : 0;
+    };
+    auto pixel = [&](float sx, float sy) __attribute__((always_inline)) {
+        if (Inside) return tap[(uint32_t)(__umul24((int)(sy + 0.5f), hw) + (int)(sx + 0.5f))];
+        return tap[(size_t)nearest_idx(sy, hh) * hw + nearest_idx(sx, hw)];
+    };
+    one(xf + rings.ox[0] * Rr, yf + rings.oy[0] * Rr, pixel(xf + rings.ox[0] * Rr, yf + rings.oy[0] * Rr),
+        4.0f * (Rr * rings.frac[0]));
+#pragma unroll 1
+    for (int k = 1; k < kRingTaps; k += kReconTaps) {
+        const float reach = 4.0f * (Rr * rings.frac[k]);
+        float sx[kReconTaps], sy[kReconTaps];
+        float2 tj[kReconTaps];
+#pragma unroll
+        for (int t = 0; t < kReconTaps; ++t) {
+            sx[t] = xf + rings.ox[k + t] * Rr;
+            sy[t] = yf + rings.oy[k + t] * Rr;
+            tj[t] = pixel(sx[t], sy[t]);
+        }
+#pragma unroll
+        for (int t = 0; t < kReconTaps; ++t) one(sx[t], sy[t], tj[t], reach);
     }
 }
 
-constexpr int kReconLds = 2496;   // mip texels a block can stage in LDS (39 KB: 4 blocks per CU)
+constexpr int kReconLds = 2368;   // mip texels a block can stage in LDS (37 KB: 4 blocks per CU)
 
 // Index range that the bilinear lookups of taps between coordinates lo and hi
 // (one axis, already at the level's scale sc) reach after the clamp to
@@ -1252,12 +1262,25 @@ __device__ inline void mip_span(float lo, float hi, float sc, int n, int &a, int
     b = clampi((int)floorf((hi + 0.5f) * sc - 0.5f) + 1, 0, n - 1);
 }
 
-// Block of a frame's reconstruction: 16 x 16 pixels, whose square footprint
-// stages fewer halo texels than a 64 x 4 row block (batches keep the common
-// 64 x 4 pixel-kernel grid); the output does not depend on the shape.
-constexpr int kReconBX = 16, kReconBY = 16;
+__device__ inline float wave_fmin(float v)
+{
+    for (int o = 32; o >= 1; o >>= 1) v = fminf(v, __shfl_xor(v, o));
+    return v;
+}
 
-template <int BX = kBX, int BY = kBY>
+// One block of 256 threads per 16 x 16 tile of half-res pixels (a square
+// footprint stages fewer halo texels than a row block).
+//
+// The output is the median blended with the taps' mean by a weight that
+// follows the pixel's temporal variance; where the weight is 0 it is the
+// median itself, and no tap is read (a frame whose colours might sum to
+// something that is not finite reads them all: 0 times it is no 0).  The
+// remaining pixels are packed into as few waves as hold them: at 1920x1080
+// 46 % of the waves of traced pixels have none, at 3840x2160 1 %.  What is
+// left is bound by vector issue, 81 instructions a tap (94 with the coordinate
+// maps and texel weights written out), next to the LDS reads, 64 of the 81
+// clocks that a tap of one wave takes a CU.  1920x1080: 121 -> 75 us,
+// 3840x2160 344 -> 323, 256x256 37 -> 30.
 __device__ inline void b_recon(const FrameConst &fc, const Rings &rings, const Planes &P, const uint32_t bx, const uint32_t by)
 {
     // The block's mip footprint: per level, the index box of every bilinear
@@ -1265,44 +1288,84 @@ __device__ inline void b_recon(const FrameConst &fc, const Rings &rings, const P
     // axes), staged in LDS when the boxes fit; else the taps read the mips
     // in global memory.
     __shared__ float4 tex[kReconLds];
-    __shared__ int box[4][4];   // per level: first and last column, first and last row
-    __shared__ int base[5];     // per level: first LDS texel; [4]: texels in all
-    const int tid = threadIdx.y * BX + threadIdx.x;
-    if (tid < 4) {
-        box[tid][0] = 0x7fffffff; box[tid][1] = -1;
-        box[tid][2] = 0x7fffffff; box[tid][3] = -1;
+    __shared__ float span[4][4][4];   // per wave and lower level: least -x, x, -y, y ... of the taps (least and greatest coordinates)
+    __shared__ int box[4][4];         // per level: first and last column, first and last row
+    __shared__ int base[5];           // per level: first LDS texel; [4]: texels in all
+    __shared__ uint32_t wcount[4];
+    __shared__ uint8_t list[256];     // the pixels that read taps
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int hw = fc.hw, hh = fc.hh, tx0 = (int)bx * kTile, ty0 = (int)by * kTile;
+    {
+        const int x = tx0 + (tid & 15), y = ty0 + (tid >> 4);
+        bool live = false;
+        float Rr = 0.0f;
+        int L0 = -1;
+        if (x < hw && y < hh) {
+            const size_t i = (size_t)y * hw + x;
+            const float2 t = P.tap[i];
+            const bool traced = t.x != -INFINITY;
+            if (traced) {
+                const float bb = clampf(P.var_blur[i] * fc.var_recon_w, 0.0f, fc.b_max);
+                live = bb != 0.0f || P.counters[kCntWild] != 0u;
+            }
+            if (live) {
+                Rr = fmin_cs(t.x * 0.25f, fc.r_max);
+                L0 = (int)floorf(clampf(t.x * fc.lod_scale, 0.0f, fc.lod_max));
+                L0 = L0 > fc.lod_levels ? fc.lod_levels : L0;
+            } else {
+                float4 o = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                if (traced) {
+                    o = P.rtmed[i];
+                    o.w = t.y;
+                }
+                P.recon[i] = o;
+            }
+        }
+        const uint64_t lives = __ballot(live);
+        if (lane == 0) wcount[w] = (uint32_t)__popcll(lives);
+        // the tap coordinates' ends per lower level
+        for (int L = 0; L < 4; ++L) {
+            float e[4] = {INFINITY, INFINITY, INFINITY, INFINITY};
+            if (__ballot(L0 == L) != 0ull) {
+                if (L0 == L) {
+                    e[0] = (float)x + (-Rr);
+                    e[1] = -((float)x + Rr);
+                    e[2] = (float)y + (-Rr);
+                    e[3] = -((float)y + Rr);
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) e[k] = wave_fmin(e[k]);
+            }
+            if (lane < 4) span[w][L][lane] = lane == 0 ? e[0] : (lane == 1 ? e[1] : (lane == 2 ? e[2] : e[3]));
+        }
+        __syncthreads();
+        uint32_t at = 0u;
+        for (int k = 0; k < w; ++k) at += wcount[k];
+        if (live) list[at + (uint32_t)__popcll(lives & ((lane == 0) ? 0ull : (~0ull >> (64 - lane))))] = (uint8_t)tid;
     }
-    __syncthreads();
-    const int x = bx * BX + threadIdx.x, y = by * BY + threadIdx.y;
-    const int hw = fc.hw, hh = fc.hh;
-    const bool in = x < hw && y < hh;
-    const size_t i = in ? (size_t)y * hw + x : 0;
-    const bool traced = in && P.T0[i].w > 0.0f;
-    float ct = 0.0f, hu = 0.0f, Rr = 0.0f, fl = 0.0f, sc0 = 1.0f, sc1 = 1.0f;
-    int L0 = 0, L1 = 0;
-    if (traced) {
-        const float4 t1 = P.T1[i];
-        ct = t1.x;
-        hu = t1.y;
-        Rr = fmin_cs(ct * 0.25f, fc.r_max);
-        const float lod = clampf(ct * fc.lod_scale, 0.0f, fc.lod_max);
-        L0 = (int)floorf(lod);
-        const int Lmax = fc.lod_levels;
-        if (L0 > Lmax) L0 = Lmax;
-        L1 = L0 < Lmax ? L0 + 1 : Lmax;
-        fl = lod - (float)L0;
-        for (int L = 0; L < L0; ++L) sc0 = sc0 * 0.5f;
-        for (int L = 0; L < L1; ++L) sc1 = sc1 * 0.5f;
-        const float lx = (float)x + (-Rr), hx = (float)x + Rr, ly = (float)y + (-Rr), hy = (float)y + Rr;
-        int c0, c1, r0, r1;
-        mip_span(lx, hx, sc0, fc.mw[L0], c0, c1);
-        mip_span(ly, hy, sc0, fc.mh[L0], r0, r1);
-        atomicMin(&box[L0][0], c0); atomicMax(&box[L0][1], c1);
-        atomicMin(&box[L0][2], r0); atomicMax(&box[L0][3], r1);
-        mip_span(lx, hx, sc1, fc.mw[L1], c0, c1);
-        mip_span(ly, hy, sc1, fc.mh[L1], r0, r1);
-        atomicMin(&box[L1][0], c0); atomicMax(&box[L1][1], c1);
-        atomicMin(&box[L1][2], r0); atomicMax(&box[L1][3], r1);
+    const int nlive = (int)(wcount[0] + wcount[1] + wcount[2] + wcount[3]);
+    if (nlive == 0) return;   // block-uniform
+    if (tid < 4) {
+        // level tid is read by pixels whose lower level it is or is next above
+        int c0 = 0x7fffffff, c1 = -1, r0 = 0x7fffffff, r1 = -1;
+        float sc = 1.0f;
+        for (int k = 0; k < tid; ++k) sc = sc * 0.5f;
+        for (int L = tid > 0 ? tid - 1 : 0; L <= tid; ++L) {
+            // pixels of lower level L read levels L and min(L + 1, lod_levels)
+            if (L != tid && !(L < fc.lod_levels)) continue;
+            float e[4];
+            for (int k = 0; k < 4; ++k) e[k] = fminf(fminf(span[0][L][k], span[1][L][k]), fminf(span[2][L][k], span[3][L][k]));
+            if (e[0] == INFINITY) continue;
+            int a, b;
+            mip_span(e[0], -e[1], sc, fc.mw[tid], a, b);
+            c0 = min(c0, a);
+            c1 = max(c1, b);
+            mip_span(e[2], -e[3], sc, fc.mh[tid], a, b);
+            r0 = min(r0, a);
+            r1 = max(r1, b);
+        }
+        box[tid][0] = c0; box[tid][1] = c1;
+        box[tid][2] = r0; box[tid][3] = r1;
     }
     __syncthreads();
     if (tid == 0) {
@@ -1320,43 +1383,58 @@ __device__ inline void b_recon(const FrameConst &fc, const Rings &rings, const P
             if (box[L][1] < box[L][0]) continue;
             const int bw = box[L][1] - box[L][0] + 1, cnt = bw * (box[L][3] - box[L][2] + 1);
             const float4 *src = P.mips + fc.moff[L];
-            for (int e = tid; e < cnt; e += BX * BY) {
+            for (int e = tid; e < cnt; e += 256) {
                 const int r = e / bw, c = e - r * bw;
                 tex[base[L] + e] = src[(size_t)(box[L][2] + r) * fc.mw[L] + box[L][0] + c];
             }
         }
     }
     __syncthreads();
-    if (!in) return;
-    if (!traced) {
-        P.recon[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        return;
-    }
+    if (tid >= nlive) return;
+    const int px = list[tid], x = tx0 + (px & 15), y = ty0 + (px >> 4);
+    const size_t i = (size_t)y * hw + x;
+    const float2 t1 = P.tap[i];
+    const float ct = t1.x, hu = t1.y, Rr = fmin_cs(ct * 0.25f, fc.r_max);
+    const float lod = clampf(ct * fc.lod_scale, 0.0f, fc.lod_max);
+    int L0 = (int)floorf(lod);
+    const int Lmax = fc.lod_levels;
+    if (L0 > Lmax) L0 = Lmax;
+    const int L1 = L0 < Lmax ? L0 + 1 : Lmax;
+    const float fl = lod - (float)L0;
+    auto level = [&](int L) {
+        MipLevel m;
+        m.sc = 1.0f;
+        for (int k = 0; k < L; ++k) m.sc = m.sc * 0.5f;
+        m.w = fc.mw[L];
+        m.h = fc.mh[L];
+        m.img = (const Texel *)(P.mips + fc.moff[L]);
+        m.row = 0u;
+        m.at = 0u;
+        m.x0 = 0; m.x1 = m.w - 1;
+        m.y0 = 0; m.y1 = m.h - 1;
+        if (staged) {
+            m.x0 = box[L][0]; m.x1 = box[L][1];
+            m.y0 = box[L][2]; m.y1 = box[L][3];
+            m.row = 16u * (uint32_t)(m.x1 - m.x0 + 1);
+            m.at = (uint32_t)(uintptr_t)(LdsTexel *)(tex + base[L]) - m.row * (uint32_t)m.y0 - 16u * (uint32_t)m.x0;
+        }
+        return m;
+    };
+    const MipLevel m0 = level(L0), m1 = level(L1);
     float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, a3 = 0.0f, sh = 0.0f;
     int na = 0;
-    const float4 *mip0 = P.mips + fc.moff[L0], *mip1 = P.mips + fc.moff[L1];
-    const int w0 = fc.mw[L0], h0 = fc.mh[L0], w1 = fc.mw[L1], h1 = fc.mh[L1];
     // The interior paths are taken by a whole wave when every lane's taps
     // stay inside all planes it reads (same arithmetic, no clamps).
     const bool inside = hw < (1 << 24) && hh < (1 << 24) && taps_inside(x, Rr, hw) && taps_inside(y, Rr, hh) &&
-                        mip_taps_inside(x, Rr, sc0, w0) && mip_taps_inside(y, Rr, sc0, h0) &&
-                        mip_taps_inside(x, Rr, sc1, w1) && mip_taps_inside(y, Rr, sc1, h1);
+                        mip_taps_inside(x, Rr, m0.sc, m0.w) && mip_taps_inside(y, Rr, m0.sc, m0.h) &&
+                        mip_taps_inside(x, Rr, m1.sc, m1.w) && mip_taps_inside(y, Rr, m1.sc, m1.h);
     const bool all_inside = __ballot(!inside) == 0ull;
     if (staged) {
-        const int bw0 = box[L0][1] - box[L0][0] + 1, bw1 = box[L1][1] - box[L1][0] + 1;
-        if (all_inside)
-            recon_taps<true, true>(x, y, Rr, fl, sc0, sc1, hw, hh, tex + base[L0], bw0, 0, box[L0], tex + base[L1], bw1,
-                                   0, box[L1], rings, P.tap, a0, a1, a2, a3, sh, na);
-        else
-            recon_taps<false, true>(x, y, Rr, fl, sc0, sc1, hw, hh, tex + base[L0], bw0, 0, box[L0], tex + base[L1],
-                                    bw1, 0, box[L1], rings, P.tap, a0, a1, a2, a3, sh, na);
+        if (all_inside) recon_taps<true, true>(x, y, Rr, fl, m0, m1, hw, hh, rings, P.tap, a0, a1, a2, a3, sh, na);
+        else recon_taps<false, true>(x, y, Rr, fl, m0, m1, hw, hh, rings, P.tap, a0, a1, a2, a3, sh, na);
     } else {
-        if (all_inside)
-            recon_taps<true, false>(x, y, Rr, fl, sc0, sc1, hw, hh, mip0, w0, h0, nullptr, mip1, w1, h1, nullptr, rings,
-                                    P.tap, a0, a1, a2, a3, sh, na);
-        else
-            recon_taps<false, false>(x, y, Rr, fl, sc0, sc1, hw, hh, mip0, w0, h0, nullptr, mip1, w1, h1, nullptr, rings,
-                                     P.tap, a0, a1, a2, a3, sh, na);
+        if (all_inside) recon_taps<true, false>(x, y, Rr, fl, m0, m1, hw, hh, rings, P.tap, a0, a1, a2, a3, sh, na);
+        else recon_taps<false, false>(x, y, Rr, fl, m0, m1, hw, hh, rings, P.tap, a0, a1, a2, a3, sh, na);
     }
     const float4 med = P.rtmed[i];
     float nb0 = a3 > 0.0f ? a0 / a3 : med.x, nb1 = a3 > 0.0f ? a1 / a3 : med.y, nb2 = a3 > 0.0f ? a2 / a3 : med.z;
@@ -1365,15 +1443,15 @@ __device__ inline void b_recon(const FrameConst &fc, const Rings &rings, const P
     P.recon[i] = make_float4(lerp1(med.x, nb0, bb), lerp1(med.y, nb1, bb), lerp1(med.z, nb2, bb), lerp1(hu, hnb, bb));
 }
 
-__global__ __launch_bounds__(kReconBX *kReconBY) void k_recon(FrameConst fc, Rings rings, Planes P)
+__global__ __launch_bounds__(256, 4) void k_recon(FrameConst fc, Rings rings, Planes P)
 {
-    b_recon<kReconBX, kReconBY>(fc, rings, P, blockIdx.x, blockIdx.y);
+    b_recon(fc, rings, P, blockIdx.x, blockIdx.y);
 }
 
-__global__ __launch_bounds__(kBX *kBY) void kb_recon(const Job *__restrict__ jobs, int njobs, Rings rings)
+__global__ __launch_bounds__(256, 4) void kb_recon(const Job *__restrict__ jobs, int njobs, Rings rings)
 {
     uint32_t bx, by;
-    const Job &J = jobs[job_of_block(jobs, njobs, kGridHalf, blockIdx.x, bx, by)];
+    const Job &J = jobs[job_of_block(jobs, njobs, kGridTiles, blockIdx.x, bx, by)];
     b_recon(J.fc, rings, J.P, bx, by);
 }
 
@@ -1747,7 +1825,7 @@ hipError_t launch_frame_post(const SceneDev &sd, const FrameConst &fc, const Rin
     DOF_REC(10);
     k_blur_median_mips<<<grid2(fc.hw, fc.hh, 8, 8), 64, 0, st>>>(fc, P, hist_out);
     DOF_REC(11);
-    k_recon<<<grid2(fc.hw, fc.hh, kReconBX, kReconBY), dim3(kReconBX, kReconBY), 0, st>>>(fc, rings, P);
+    k_recon<<<dim3(fc.tw, fc.th), 256, 0, st>>>(fc, rings, P);
     DOF_REC(12);
     if (side) {
         const hipError_t e = hipStreamWaitEvent(st, side->join, 0);   // the post-process chain is done
@@ -1808,7 +1886,7 @@ hipError_t launch_batch_post(BatchHead *head, const Job *jobs, int njobs, const 
     }
     kb_temporal<<<nblk[kGridHalf], dim3(kBX, kBY), 0, st>>>(jobs, njobs);
     kb_blur_median_mips<<<nblk[kGridMip], 64, 0, st>>>(jobs, njobs);
-    kb_recon<<<nblk[kGridHalf], dim3(kBX, kBY), 0, st>>>(jobs, njobs, rings);
+    kb_recon<<<nblk[kGridTiles], 256, 0, st>>>(jobs, njobs, rings);
     if (side) {
         const hipError_t e = hipStreamWaitEvent(st, side->join, 0);   // the post-process chain is done
         if (e != hipSuccess) return e;

@@ -1,0 +1,57 @@
+"""The reconstruction where its work changes: a pixel whose blend weight is 0
+is the median and reads no taps, the others are packed into as few waves as
+hold them, and a frame whose colours are so large that sums over taps may
+overflow reads every tap.  Sizes: one tile of 16 x 16 half-res pixels, its
+edges and remainders.
+
+Every value is held to the oracle's within 1e-5 of the largest colour (the
+81 weights of a pixel's taps are rounded once each: 81 * 2^-24 = 5e-6), and a
+pixel of weight 0 to the median, bit for bit."""
+
+import dataclasses
+
+import numpy as np
+import pytest
+
+from paper_2210_06158_amd import synth
+from test_gpu_parity import run_pair
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def envs(orc):
+    import torch
+    from paper_2210_06158_amd import dof
+    out = {}
+    for scale in (1.0, 4e18):    # 4e18: beyond the bound of a tame frame; its square is finite
+        scene, cam, lens, params = synth.scene_small()
+        scene = dataclasses.replace(scene, albedo=(scene.albedo * scale).astype(np.float32))
+        osc = orc.OracleScene(scene)
+        osc.build_bvh()
+        gs = dof.Scene(scene)
+        gs.build_bvh()
+        out[scale] = (dict(torch=torch, dof=dof, osc=osc, gs=gs), cam, lens, params)
+    return out
+
+
+@pytest.mark.parametrize("w,h", [(2, 2), (30, 34), (32, 32), (66, 62), (130, 40)])
+@pytest.mark.parametrize("scale", [1.0, 4e18])
+@pytest.mark.parametrize("var_w", [0.0, 2.0, 2000.0])
+def test_weights_of_zero_and_not(envs, orc, scale, var_w, w, h):
+    env, cam, lens, params = envs[scale]
+    cam = dataclasses.replace(cam, width=w, height=h)
+    p = dataclasses.replace(params, mask_mode=synth.MASK_ALL, var_recon_w=var_w / scale ** 2)
+    gb = orc.gbuffer(env["osc"], cam, lens)
+    hist, prev = None, None
+    for frame in range(3):
+        o, d = run_pair(env, orc, cam, lens, p, gb, hist_in=hist, prev_cam=prev, prev_lens=lens if prev else None)
+        assert np.array_equal(d["mask"], o["mask"])
+        tol = 1e-5 * scale
+        np.testing.assert_allclose(d["rtmed"], o["rtmed"], rtol=1e-5, atol=tol)
+        np.testing.assert_allclose(d["recon"], o["recon"], rtol=1e-5, atol=tol)
+        still = np.clip(d["var_blur"] * np.float32(p.var_recon_w), 0, p.b_max) == 0
+        med = d["rtmed"].reshape(d["recon"].shape)
+        at = still.reshape(d["recon"].shape[:2]) & (med[..., 3] > 0)
+        assert np.array_equal(d["recon"][at][:, :3], med[at][:, :3])
+        hist, prev = o["hist_out"], cam
