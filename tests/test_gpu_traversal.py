@@ -47,3 +47,32 @@ def test_rays_at_the_edges_of_the_hand_out(scenes, orc, name, n):
     want, tw = orc.closest_hit(osc, o, d, use_bvh=False)
     assert np.array_equal(hit.cpu().numpy(), want)
     assert np.array_equal(t.cpu().numpy().view(np.uint32), tw.view(np.uint32))
+
+
+# one block, fewer blocks than work counters, as many, and more that they do
+# not divide; grab 100 leaves a remainder in every run's start
+@pytest.mark.parametrize("blocks", [1, 2, 7, 8, 9, 17])
+@pytest.mark.parametrize("grab", [0, 16, 100])
+def test_every_run_is_handed_out(orc, blocks, grab):
+    """131072 rays on a few blocks: every ray's hit and distance (exact)."""
+    import dataclasses
+    import torch
+    from paper_2210_06158_amd import dof
+    scene, cam, lens, params = synth.scene_small()
+    params = dataclasses.replace(params, mask_mode=synth.MASK_ALL, m=8)
+    osc = orc.OracleScene(scene)
+    osc.build_bvh()
+    gs = dof.Scene(scene)
+    gs.build_bvh()
+    gb = orc.gbuffer(osc, cam, lens)
+    want = orc.render_frame(osc, cam, lens, params, gb)
+    print(f"{blocks} blocks, runs of {grab}", flush=True)
+    fr = dof.Frame(cam.width, cam.height, params, ray_records=True, trace_blocks=blocks,
+                   knobs={"trace_grab": grab} if grab else None)
+    g = tuple(torch.from_numpy(x).cuda() for x in (gb.colour, gb.depth, gb.normal))
+    fr.render(gs, cam, lens, g, None, dof.history_alloc(cam.width, cam.height))
+    torch.cuda.synchronize()
+    d = fr.debug()
+    assert d["n_rays"] == want["n_rays"] > 128 * blocks
+    assert np.array_equal(d["ray_hit"], want["ray_hit"])
+    assert np.array_equal(d["ray_t"].view(np.uint32), want["ray_t"].view(np.uint32))
