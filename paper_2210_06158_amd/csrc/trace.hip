@@ -394,12 +394,12 @@ __device__ inline void put_ray(float4 *rec0, float2 *rec1, uint32_t r, const flo
     rec1[r] = make_float2(d[1], d[2]);
 }
 
-__device__ inline void get_ray(const float4 *rec0, const float2 *rec1, uint32_t r, WRay &w)
+__device__ inline void get_ray(const float4 *rec0, const float2 *rec1, uint32_t r, float o[3], float d[3])
 {
     const float4 a = rec0[r];
     const float2 b = rec1[r];
-    const float o[3] = {a.x, a.y, a.z}, d[3] = {a.w, b.x, b.y};
-    w = make_wray(o, d);
+    o[0] = a.x; o[1] = a.y; o[2] = a.z;
+    d[0] = a.w; d[1] = b.x; d[2] = b.y;
 }
 
 // The traversal's result of a lens ray: leaf of the closest hit (~0u: none)
@@ -414,10 +414,7 @@ __device__ inline void put_lt(uint2 *lt, uint32_t r, const Hit &h)
 __device__ inline void ray_of(const SceneArgs &S, const Planes &P, uint32_t r, float o[3], float d[3], Hit &h)
 {
     const uint2 lt = P.ray_lt[r];
-    const float4 a = P.rec0[r];
-    const float2 b = P.rec1[r];
-    o[0] = a.x; o[1] = a.y; o[2] = a.z;
-    d[0] = a.w; d[1] = b.x; d[2] = b.y;
+    get_ray(P.rec0, P.rec1, r, o, d);
     h.t = __uint_as_float(lt.y);
     h.leaf = lt.x;
     h.id = lt.x == ~0u ? ~0u : __float_as_uint(S.tris[3 * (size_t)lt.x].w);
@@ -429,7 +426,7 @@ struct LensRays {
     const float2 *rec1;
     uint2 *ray_lt;
 
-    __device__ void start(uint32_t r, WRay &w) const { get_ray(rec0, rec1, r, w); }
+    __device__ void ray(uint32_t r, float o[3], float d[3]) const { get_ray(rec0, rec1, r, o, d); }
 
     __device__ void finish(uint32_t r, const Hit &h) const { put_lt(ray_lt, r, h); }
 };
@@ -470,10 +467,10 @@ struct BatchRays {
 
     __device__ SceneArgs scene(int j) const { return jobs[j].scene; }
 
-    __device__ void start(uint32_t r, int j, WRay &w) const
+    __device__ void ray(uint32_t r, int j, float o[3], float d[3]) const
     {
         const Job &J = jobs[j];
-        get_ray(J.P.rec0, J.P.rec1, r - offsets()[j], w);
+        get_ray(J.P.rec0, J.P.rec1, r - offsets()[j], o, d);
     }
 
     __device__ void finish(uint32_t r, int j, const Hit &h) const
@@ -493,7 +490,7 @@ struct PinholeRays {
     uint32_t *normal;
     uint32_t stride;   // words per pixel of the normal image
 
-    __device__ void setup(uint32_t p, float o[3], float d[3]) const
+    __device__ void ray(uint32_t p, float o[3], float d[3]) const
     {
         const int x = (int)(p % (uint32_t)W), y = (int)(p / (uint32_t)W);
         float fv[3];
@@ -504,13 +501,6 @@ struct PinholeRays {
             d[a] = fv[a] / len;
             o[a] = view.pos[a];
         }
-    }
-
-    __device__ void start(uint32_t p, WRay &w) const
-    {
-        float o[3], d[3];
-        setup(p, o, d);
-        w = make_wray(o, d);
     }
 
     __device__ void finish(uint32_t p, const Hit &h) const
@@ -528,7 +518,7 @@ __global__ __launch_bounds__(256) void k_gbuffer_shade(SceneArgs S, SceneShade s
     const uint32_t leaf = src.normal[(size_t)p * src.stride];
     if (leaf != ~0u) {
         float o[3], d[3];
-        src.setup(p, o, d);
+        src.ray(p, o, d);
         const float t = src.depth[p];
         const ViewConst &v = src.view;
         const float P0 = o[0] + t * d[0], P1 = o[1] + t * d[1], P2 = o[2] + t * d[2];
@@ -548,15 +538,13 @@ struct RawRays {
     int32_t *hit;
     float *t;
 
-    __device__ void start(uint32_t i, WRay &w) const
+    __device__ void ray(uint32_t i, float o[3], float d[3]) const
     {
-        float o[3], d[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             o[a] = org[3 * (size_t)i + a];
             d[a] = dir[3 * (size_t)i + a];
         }
-        w = make_wray(o, d);
     }
 
     __device__ void finish(uint32_t i, const Hit &h) const
@@ -578,13 +566,6 @@ struct RefRays {
     __device__ void ray(uint32_t r, float o[3], float d[3]) const
     {
         thin_lens_ray(fc, p0 + r / spp, (uint32_t)fc.W, (uint32_t)fc.H, r % spp, o, d);
-    }
-
-    __device__ void start(uint32_t r, WRay &w) const
-    {
-        float o[3], d[3];
-        ray(r, o, d);
-        w = make_wray(o, d);
     }
 
     __device__ void finish(uint32_t r, const Hit &h) const { put_lt(lt, r, h); }
@@ -952,6 +933,14 @@ void k_traverse(SceneArgs S, Src src, uint32_t count, const uint32_t *count_ptr,
         pool = b < N ? (uint32_t)b : N;
         pool_end = N - pool < grab ? N : pool + grab;
     }
+    // The wave's next rays, one a lane: rays [first, ready) of the pool.  All
+    // lanes fetch (or make) 64 at once and a refill's lanes take theirs by
+    // shuffle, instead of each refill waiting for its own with a quarter of
+    // the lanes at work: 3840x2160 2246 -> 2193 us, the fully traced
+    // 1280x720 image, whose rays are sampled here, 2484 -> 2425.  A batch's
+    // lanes have no registers left for it.
+    float po[3] = {0.0f, 0.0f, 0.0f}, pd[3] = {0.0f, 0.0f, 0.0f};
+    uint32_t first = pool, ready = pool;
     while (true) {
         const uint64_t idle = __ballot(state >= kNoRay);
         if (!(drained && pool == pool_end) && (__popcll(idle) >= tk.refill || idle == ~0ull) && idle != 0ull) {
@@ -967,19 +956,37 @@ void k_traverse(SceneArgs S, Src src, uint32_t count, const uint32_t *count_ptr,
                 } else {
                     pool = base;
                     pool_end = N - base < grab ? N : base + grab;
+                    ready = pool;
                 }
             }
-            const uint32_t avail = pool_end - pool;
+            if (!Src::kPerLaneScene && pool == ready && pool != pool_end) {
+                first = pool;
+                ready = pool_end - pool < 64u ? pool_end : pool + 64u;
+                const uint32_t r = min(first + (uint32_t)lane, ready - 1u);
+                if constexpr (!Src::kPerLaneScene) src.ray(tk.reverse ? N - 1u - r : r, po, pd);
+            }
+            const uint32_t avail = (Src::kPerLaneScene ? pool_end : ready) - pool;
             const uint32_t rank = (uint32_t)__popcll(idle & lt);
+            float so[3], sd[3];
+            if constexpr (!Src::kPerLaneScene) {
+                const int from = (int)(pool + rank - first);   // below 64 where a ray is taken
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    so[a] = __shfl(po[a], from);
+                    sd[a] = __shfl(pd[a], from);
+                }
+            }
             if (state >= kNoRay && rank < avail) {
                 item = pool + rank;
                 if (tk.reverse) item = N - 1u - item;   // pool + rank < N
                 if constexpr (Src::kPerLaneScene) {
+                    float o[3], d[3];
                     job = src.job_of(item);
                     Sl = src.scene(job);
-                    src.start(item, job, wr);
+                    src.ray(item, job, o, d);
+                    wr = make_wray(o, d);
                 } else {
-                    src.start(item, wr);
+                    wr = make_wray(so, sd);
                 }
                 h = Hit{INFINITY, ~0u, 0u};
                 node = 0;
