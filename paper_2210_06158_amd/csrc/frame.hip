@@ -1202,54 +1202,82 @@ __device__ inline void acc_bilinear(const MipLevel &L, float x, float y, float f
     a3 = fmaf(t11.w, w11, fmaf(t01.w, w01, fmaf(t10.w, w10, fmaf(t00.w, w00, a3))));
 }
 
-// The 81 taps of one pixel in tap order, the centre and then kReconTaps at a
-// time (every ring holds a multiple of eight taps at one distance).  Two at a
-// time keep the kernel at 4 waves per SIMD without spills: 3840x2160 takes
-// 2269 us a frame with two, 2295 with one or four and 2286 with eight (3 waves).  Which texels a tap reads, and whether it counts,
-// are decided exactly as in the per-pixel definition.  Every tap's fetches are
-// issued (indices in bounds: clamped, or shown inside) and rejected taps weigh
-// 0, so the loads of several taps can be in flight at once.  A tap counts when
-// its pixel is ray traced and its CoC radius reaches the tap (pixels that are
-// not carry -inf).  The scales are powers of two, so the fused coordinate maps
-// round as a product and a difference would.
-constexpr int kReconTaps = 2;
+// What a pixel's taps add up to.
+struct TapSums {
+    float a0, a1, a2, a3;   // weighted colour and weight of the mip samples
+    float sh;               // hit ratios of the taps that count
+    int n;                  // how many count
 
+    __device__ void add(const TapSums &u)
+    {
+        a0 = a0 + u.a0; a1 = a1 + u.a1; a2 = a2 + u.a2; a3 = a3 + u.a3;
+        sh = sh + u.sh;
+        n += u.n;
+    }
+};
+
+constexpr int kReconTaps = 2;      // ring taps an iteration
+constexpr int kReconQuarter = 20;  // ring taps of a quarter
+
+// Quarters [q0, q1) of one pixel's 81 taps in tap order (the first quarter
+// starts with the centre), each summed by itself, kReconTaps at a time (every ring starts at an odd tap and holds
+// an even number of taps at one distance).  Two at a time keep the kernel at 4
+// waves per SIMD without spills: 3840x2160 takes 2269 us a frame with two,
+// 2295 with one or four and 2286 with eight (3 waves).  Which texels a tap
+// reads, and whether it counts, are decided exactly as in the per-pixel
+// definition.  Every tap's fetches are issued (indices in bounds: clamped, or
+// shown inside) and rejected taps weigh 0, so the loads of several taps can be
+// in flight at once.  A tap counts when its pixel is ray traced and its CoC
+// radius reaches the tap (pixels that are not carry -inf).  The scales are
+// powers of two, so the fused coordinate maps round as a product and a
+// difference would.
 template <bool Inside, bool Lds>
-__device__ inline void recon_taps(int x, int y, float Rr, float fl, const MipLevel &L0, const MipLevel &L1, int hw, int hh,
-                                  const Rings &rings, const float2 *tap, float &a0, float &a1, float &a2, float &a3,
-                                  float &sh, int &na)
+__device__ inline TapSums recon_taps(int q0, int q1, int x, int y, float Rr, float fl, const MipLevel &L0, const MipLevel &L1, int hw,
+                                     int hh, const Rings &rings, const float2 *tap)
 {
+    TapSums s = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0}, sum = s;
     const float omf = 1.0f - fl, xf = (float)x, yf = (float)y;
     auto one = [&](float sx, float sy, float2 tj, float reach) __attribute__((always_inline)) {
         const bool ok = tj.x >= reach;   // CoC diameter against four times the distance: a quarter of it is exact
         const float cx = sx + 0.5f, cy = sy + 0.5f;
-        acc_bilinear<Inside, Lds>(L0, fmaf(cx, L0.sc, -0.5f), fmaf(cy, L0.sc, -0.5f), ok ? omf : 0.0f, a0, a1, a2, a3);
-        acc_bilinear<Inside, Lds>(L1, fmaf(cx, L1.sc, -0.5f), fmaf(cy, L1.sc, -0.5f), ok ? fl : 0.0f, a0, a1, a2, a3);
-        sh = sh + (ok ? tj.y : 0.0f);
-        na += ok ? 1 : 0;
+        acc_bilinear<Inside, Lds>(L0, fmaf(cx, L0.sc, -0.5f), fmaf(cy, L0.sc, -0.5f), ok ? omf : 0.0f, s.a0, s.a1, s.a2, s.a3);
+        acc_bilinear<Inside, Lds>(L1, fmaf(cx, L1.sc, -0.5f), fmaf(cy, L1.sc, -0.5f), ok ? fl : 0.0f, s.a0, s.a1, s.a2, s.a3);
+        s.sh = s.sh + (ok ? tj.y : 0.0f);
+        s.n += ok ? 1 : 0;
     };
     auto pixel = [&](float sx, float sy) __attribute__((always_inline)) {
         if (Inside) return tap[(uint32_t)(__umul24((int)(sy + 0.5f), hw) + (int)(sx + 0.5f))];
         return tap[(size_t)nearest_idx(sy, hh) * hw + nearest_idx(sx, hw)];
     };
-    one(xf + rings.ox[0] * Rr, yf + rings.oy[0] * Rr, pixel(xf + rings.ox[0] * Rr, yf + rings.oy[0] * Rr),
-        4.0f * (Rr * rings.frac[0]));
+    if (q0 == 0)
+        one(xf + rings.ox[0] * Rr, yf + rings.oy[0] * Rr, pixel(xf + rings.ox[0] * Rr, yf + rings.oy[0] * Rr),
+            4.0f * (Rr * rings.frac[0]));
 #pragma unroll 1
-    for (int k = 1; k < kRingTaps; k += kReconTaps) {
-        const float reach = 4.0f * (Rr * rings.frac[k]);
-        float sx[kReconTaps], sy[kReconTaps];
-        float2 tj[kReconTaps];
+    for (int q = q0; q < q1; ++q) {
+        const int first = 1 + q * kReconQuarter;
+#pragma unroll 1
+        for (int k = first; k < first + kReconQuarter; k += kReconTaps) {
+            const float reach = 4.0f * (Rr * rings.frac[k]);
+            float sx[kReconTaps], sy[kReconTaps];
+            float2 tj[kReconTaps];
 #pragma unroll
-        for (int t = 0; t < kReconTaps; ++t) {
-            sx[t] = xf + rings.ox[k + t] * Rr;
-            sy[t] = yf + rings.oy[k + t] * Rr;
-            tj[t] = pixel(sx[t], sy[t]);
+            for (int t = 0; t < kReconTaps; ++t) {
+                sx[t] = xf + rings.ox[k + t] * Rr;
+                sy[t] = yf + rings.oy[k + t] * Rr;
+                tj[t] = pixel(sx[t], sy[t]);
+            }
+#pragma unroll
+            for (int t = 0; t < kReconTaps; ++t) one(sx[t], sy[t], tj[t], reach);
         }
-#pragma unroll
-        for (int t = 0; t < kReconTaps; ++t) one(sx[t], sy[t], tj[t], reach);
+        sum.add(s);
+        s = TapSums{0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0};
     }
+    return sum;
 }
 
+static_assert(1 + 4 * kReconQuarter == kRingTaps && kReconQuarter % kReconTaps == 0, "whole quarters");
+
+constexpr int kReconSplit = 768;  // 16 x 16 tiles below which a frame's reconstruction takes 8 x 8 ones
 constexpr int kReconLds = 2368;   // mip texels a block can stage in LDS (37 KB: 4 blocks per CU)
 
 // Index range that the bilinear lookups of taps between coordinates lo and hi
@@ -1268,8 +1296,11 @@ __device__ inline float wave_fmin(float v)
     return v;
 }
 
-// One block of 256 threads per 16 x 16 tile of half-res pixels (a square
-// footprint stages fewer halo texels than a row block).
+// One block of 256 threads per tile of kSide x kSide half-res pixels (a square
+// footprint stages fewer halo texels than a row block): 16 x 16, a lane per
+// pixel, or 8 x 8, whose pixels' taps the four waves share, a quarter each.
+// Both add the quarters' sums in the same order, so a pixel's value does not
+// depend on the tile.
 //
 // The output is the median blended with the taps' mean by a weight that
 // follows the pixel's temporal variance; where the weight is 0 it is the
@@ -1281,6 +1312,7 @@ __device__ inline float wave_fmin(float v)
 // maps and texel weights written out), next to the LDS reads, 64 of the 81
 // clocks that a tap of one wave takes a CU.  1920x1080: 121 -> 75 us,
 // 3840x2160 344 -> 323, 256x256 37 -> 30.
+template <int kSide>
 __device__ inline void b_recon(const FrameConst &fc, const Rings &rings, const Planes &P, const uint32_t bx, const uint32_t by)
 {
     // The block's mip footprint: per level, the index box of every bilinear
@@ -1294,13 +1326,13 @@ __device__ inline void b_recon(const FrameConst &fc, const Rings &rings, const P
     __shared__ uint32_t wcount[4];
     __shared__ uint8_t list[256];     // the pixels that read taps
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int hw = fc.hw, hh = fc.hh, tx0 = (int)bx * kTile, ty0 = (int)by * kTile;
+    const int hw = fc.hw, hh = fc.hh, tx0 = (int)bx * kSide, ty0 = (int)by * kSide;
     {
-        const int x = tx0 + (tid & 15), y = ty0 + (tid >> 4);
+        const int x = tx0 + tid % kSide, y = ty0 + tid / kSide;
         bool live = false;
         float Rr = 0.0f;
         int L0 = -1;
-        if (x < hw && y < hh) {
+        if (x < hw && y < hh && tid < kSide * kSide) {
             const size_t i = (size_t)y * hw + x;
             const float2 t = P.tap[i];
             const bool traced = t.x != -INFINITY;
@@ -1390,8 +1422,9 @@ __device__ inline void b_recon(const FrameConst &fc, const Rings &rings, const P
         }
     }
     __syncthreads();
-    if (tid >= nlive) return;
-    const int px = list[tid], x = tx0 + (px & 15), y = ty0 + (px >> 4);
+    const int slot = kSide == 16 ? tid : lane;
+    if (kSide == 16 && slot >= nlive) return;
+    const int px = list[slot < nlive ? slot : 0], x = tx0 + px % kSide, y = ty0 + px / kSide;
     const size_t i = (size_t)y * hw + x;
     const float2 t1 = P.tap[i];
     const float ct = t1.x, hu = t1.y, Rr = fmin_cs(ct * 0.25f, fc.r_max);
@@ -1421,38 +1454,47 @@ __device__ inline void b_recon(const FrameConst &fc, const Rings &rings, const P
         return m;
     };
     const MipLevel m0 = level(L0), m1 = level(L1);
-    float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, a3 = 0.0f, sh = 0.0f;
-    int na = 0;
     // The interior paths are taken by a whole wave when every lane's taps
     // stay inside all planes it reads (same arithmetic, no clamps).
     const bool inside = hw < (1 << 24) && hh < (1 << 24) && taps_inside(x, Rr, hw) && taps_inside(y, Rr, hh) &&
                         mip_taps_inside(x, Rr, m0.sc, m0.w) && mip_taps_inside(y, Rr, m0.sc, m0.h) &&
                         mip_taps_inside(x, Rr, m1.sc, m1.w) && mip_taps_inside(y, Rr, m1.sc, m1.h);
     const bool all_inside = __ballot(!inside) == 0ull;
+    const int q0 = kSide == 16 ? 0 : __builtin_amdgcn_readfirstlane(w), q1 = kSide == 16 ? 4 : q0 + 1;
+    TapSums s;
     if (staged) {
-        if (all_inside) recon_taps<true, true>(x, y, Rr, fl, m0, m1, hw, hh, rings, P.tap, a0, a1, a2, a3, sh, na);
-        else recon_taps<false, true>(x, y, Rr, fl, m0, m1, hw, hh, rings, P.tap, a0, a1, a2, a3, sh, na);
+        if (all_inside) s = recon_taps<true, true>(q0, q1, x, y, Rr, fl, m0, m1, hw, hh, rings, P.tap);
+        else s = recon_taps<false, true>(q0, q1, x, y, Rr, fl, m0, m1, hw, hh, rings, P.tap);
     } else {
-        if (all_inside) recon_taps<true, false>(x, y, Rr, fl, m0, m1, hw, hh, rings, P.tap, a0, a1, a2, a3, sh, na);
-        else recon_taps<false, false>(x, y, Rr, fl, m0, m1, hw, hh, rings, P.tap, a0, a1, a2, a3, sh, na);
+        if (all_inside) s = recon_taps<true, false>(q0, q1, x, y, Rr, fl, m0, m1, hw, hh, rings, P.tap);
+        else s = recon_taps<false, false>(q0, q1, x, y, Rr, fl, m0, m1, hw, hh, rings, P.tap);
+    }
+    if constexpr (kSide != 16) {
+        __shared__ TapSums part[3][64];
+        if (w > 0) part[w - 1][lane] = s;
+        __syncthreads();
+        if (w > 0 || lane >= nlive) return;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) s.add(part[q][lane]);
     }
     const float4 med = P.rtmed[i];
-    float nb0 = a3 > 0.0f ? a0 / a3 : med.x, nb1 = a3 > 0.0f ? a1 / a3 : med.y, nb2 = a3 > 0.0f ? a2 / a3 : med.z;
-    float hnb = na > 0 ? sh / (float)na : hu;
+    float nb0 = s.a3 > 0.0f ? s.a0 / s.a3 : med.x, nb1 = s.a3 > 0.0f ? s.a1 / s.a3 : med.y, nb2 = s.a3 > 0.0f ? s.a2 / s.a3 : med.z;
+    float hnb = s.n > 0 ? s.sh / (float)s.n : hu;
     float bb = clampf(P.var_blur[i] * fc.var_recon_w, 0.0f, fc.b_max);
     P.recon[i] = make_float4(lerp1(med.x, nb0, bb), lerp1(med.y, nb1, bb), lerp1(med.z, nb2, bb), lerp1(hu, hnb, bb));
 }
 
+template <int kSide>
 __global__ __launch_bounds__(256, 4) void k_recon(FrameConst fc, Rings rings, Planes P)
 {
-    b_recon(fc, rings, P, blockIdx.x, blockIdx.y);
+    b_recon<kSide>(fc, rings, P, blockIdx.x, blockIdx.y);
 }
 
 __global__ __launch_bounds__(256, 4) void kb_recon(const Job *__restrict__ jobs, int njobs, Rings rings)
 {
     uint32_t bx, by;
     const Job &J = jobs[job_of_block(jobs, njobs, kGridTiles, blockIdx.x, bx, by)];
-    b_recon(J.fc, rings, J.P, bx, by);
+    b_recon<16>(J.fc, rings, J.P, bx, by);
 }
 
 // ---------------------------------------------------------------- A14
@@ -1825,7 +1867,11 @@ hipError_t launch_frame_post(const SceneDev &sd, const FrameConst &fc, const Rin
     DOF_REC(10);
     k_blur_median_mips<<<grid2(fc.hw, fc.hh, 8, 8), 64, 0, st>>>(fc, P, hist_out);
     DOF_REC(11);
-    k_recon<<<dim3(fc.tw, fc.th), 256, 0, st>>>(fc, rings, P);
+    // Four waves to a pixel where the 16 x 16 tiles leave the chip idle (it
+    // holds 1024 blocks): 256x256 127 -> 114 us a frame, 800x600 166 -> 159;
+    // at 960x960 (900 tiles) both take as long, at 1920x1080 450 -> 468.
+    if (fc.tw * fc.th < kReconSplit) k_recon<8><<<grid2(fc.hw, fc.hh, 8, 8), 256, 0, st>>>(fc, rings, P);
+    else k_recon<16><<<dim3(fc.tw, fc.th), 256, 0, st>>>(fc, rings, P);
     DOF_REC(12);
     if (side) {
         const hipError_t e = hipStreamWaitEvent(st, side->join, 0);   // the post-process chain is done

@@ -778,7 +778,7 @@ constexpr int kDropChunk = 8;    // oldest stack entries dropped when the LDS st
 // Occupancy: 70 VGPRs a lane would let seven waves share a SIMD; the 24-entry
 // stack's LDS allows six (12.5 KB a block), the 16-entry one's seven.  A
 // batch's lanes also hold their scene's pointers; asking for six waves (80
-// VGPRs, none spilled) makes a 32-session batch 3.6 % faster.
+// VGPRs) makes a 32-session batch 3.6 % faster.
 // Orders a wave's own LDS accesses (they execute in order; this keeps the
 // compiler from moving or caching them).
 __device__ inline void wave_sync()

@@ -55,3 +55,16 @@ def test_weights_of_zero_and_not(envs, orc, scale, var_w, w, h):
         at = still.reshape(d["recon"].shape[:2]) & (med[..., 3] > 0)
         assert np.array_equal(d["recon"][at][:, :3], med[at][:, :3])
         hist, prev = o["hist_out"], cam
+
+
+# 756 and 784 tiles of 16 x 16: the last frame whose pixels' taps four waves
+# share, and one with a lane per pixel (a batch's items always have that, and
+# are held to the frame's bits elsewhere)
+@pytest.mark.parametrize("w,h", [(896, 864), (896, 896)])
+def test_either_tile(envs, orc, w, h):
+    env, cam, lens, params = envs[1.0]
+    cam = dataclasses.replace(cam, width=w, height=h)
+    gb = orc.gbuffer(env["osc"], cam, lens)
+    o, d = run_pair(env, orc, cam, lens, params, gb)
+    np.testing.assert_allclose(d["rtmed"], o["rtmed"], rtol=1e-5, atol=1e-5)
+    np.testing.assert_allclose(d["recon"], o["recon"], rtol=1e-5, atol=1e-5)
