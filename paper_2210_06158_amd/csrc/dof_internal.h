@@ -141,6 +141,7 @@ struct ScratchLayout {
     int64_t nchunks;
 };
 
+constexpr int kSmallFrame = 1 << 17;   // half-res pixels up to which one launch compacts the mask and generates the rays
 constexpr int kChunk = 1024;   // pixels per compaction chunk (256 threads x 4)
 
 // Device pointers of every plane of one frame (from its scratch layout).
@@ -283,6 +284,9 @@ int blocks_for(int blocks, int64_t rays);   // of `blocks`, as many as a launch 
 hipError_t launch_trace(const SceneDev &s, const FrameConst &fc, const ScratchLayout &L, char *scratch,
                         int blocks, hipStream_t st);
 // the ray records of every thin-lens ray of the frame (after the compaction)
+// compaction and ray generation of a frame of at most kSmallFrame half-res
+// pixels, its mask aligned to 4 bytes
+hipError_t launch_compact_small(const FrameConst &fc, const ScratchLayout &L, char *scratch, const uint8_t *mask, hipStream_t st);
 hipError_t launch_raygen(const FrameConst &fc, const ScratchLayout &L, char *scratch, hipStream_t st);
 // hit record, distance, shaded colour and position of every ray (after the traversal)
 // Job of a block of a batched launch: the last job whose first block in grid

@@ -1836,9 +1836,14 @@ hipError_t launch_frame_pre(const FrameConst &fc, const Rings &rings, const Scra
         k_mask<<<dim3(fc.tw, fc.th), dim3(kTile, kTile), 0, st>>>(fc, P, hist_in, mask);
     }
     DOF_REC(6);
-    k_compact_count<<<(unsigned)L.nchunks, 256, 0, st>>>(np, mask, P);
-    k_compact_scatter<<<(unsigned)L.nchunks, 256, 0, st>>>(np, mask, P);
-    const hipError_t e = launch_raygen(fc, L, scratch, st);
+    hipError_t e;
+    if (np <= kSmallFrame && reinterpret_cast<uintptr_t>(mask) % 4 == 0) {
+        e = launch_compact_small(fc, L, scratch, mask, st);
+    } else {
+        k_compact_count<<<(unsigned)L.nchunks, 256, 0, st>>>(np, mask, P);
+        k_compact_scatter<<<(unsigned)L.nchunks, 256, 0, st>>>(np, mask, P);
+        e = launch_raygen(fc, L, scratch, st);
+    }
     if (e != hipSuccess) return e;
     DOF_REC(7);
     if (side) {

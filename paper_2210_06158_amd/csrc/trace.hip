@@ -702,6 +702,88 @@ __global__ __launch_bounds__(kGenTB) void kb_raygen(const Job *__restrict__ jobs
     }
 }
 
+// The compaction and the ray generation of a small frame in one launch: one
+// block per 256 pixels in row-major order, whose first queue position and ray
+// are the sums over the mask before them.  Ranks come from wave ballots (masked
+// pixels) and wave prefix sums (rays), so the queue is ascending and the
+// block's rays are one contiguous range, which it then generates itself, a map
+// from ray to pixel kept in LDS.  A small frame's time is its launches': 7 us
+// instead of the three kernels' 13 and two gaps.  256x256 113 -> 109 us a
+// frame, 640x480 144 -> 137, 800x600 159 -> 154; the sums over the mask grow
+// with the square of the frame, and at 960x960 (230400 half-res pixels) it is
+// 218 -> 220: hence kSmallFrame.
+constexpr int kSmallRays = 4096;   // rays of a window (16 per pixel)
+
+__global__ __launch_bounds__(kGenTB) void k_compact_small(FrameConst fc, Planes P, const uint8_t *__restrict__ mask)
+{
+    __shared__ uint32_t wp[4], wr[4];
+    __shared__ uint8_t s_pix[kSmallRays];   // ray of the window -> pixel of the block
+    __shared__ uint32_t s_base[kGenTB];     // pixel of the block -> its first ray
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const uint32_t hw = (uint32_t)fc.hw, hh = (uint32_t)fc.hh, np = hw * hh, q0 = blockIdx.x * kGenTB, q = q0 + (uint32_t)tid;
+    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    // the traversal's counters start the frame at zero
+    if (blockIdx.x == 0 && tid < kWorkParts) {
+        uint32_t *c = P.counters + kCntWork + tid * kWorkStride;
+        c[0] = 0u;
+        for (int k = 0; k < kStatWords; ++k) c[kStatAt + k] = 0u;
+        if (tid == 0) P.counters[kCntWild] = 0u;
+    }
+    const uint32_t n = q < np ? mask[q] : 0u;
+    uint32_t before = 0, rays_before = 0;   // four pixels a word: the launch has shown the mask aligned
+    const uint32_t *words = reinterpret_cast<const uint32_t *>(mask);
+#pragma unroll 8
+    for (uint32_t i = (uint32_t)tid; i < q0 / 4; i += kGenTB) {
+        const uint32_t v = words[i];
+        before += (uint32_t)__popc((((v & 0x7f7f7f7fu) + 0x7f7f7f7fu) | v) & 0x80808080u);
+        rays_before = __builtin_amdgcn_sad_u8(v, 0u, rays_before);
+    }
+    for (int o = 32; o >= 1; o >>= 1) {
+        before += __shfl_xor(before, o);
+        rays_before += __shfl_xor(rays_before, o);
+    }
+    const uint64_t bal = __ballot(n > 0u);
+    uint32_t incl = n;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t u = __shfl_up(incl, o);
+        if (lane >= o) incl += u;
+    }
+    __shared__ uint32_t bp[4], br[4];
+    if (lane == 63) {
+        wp[w] = (uint32_t)__popcll(bal);
+        wr[w] = incl;
+        bp[w] = before;
+        br[w] = rays_before;
+    }
+    __syncthreads();
+    const uint32_t p0 = bp[0] + bp[1] + bp[2] + bp[3], r0 = br[0] + br[1] + br[2] + br[3];
+    const uint32_t rays = wr[0] + wr[1] + wr[2] + wr[3];
+    uint32_t pos = p0 + (uint32_t)__popcll(bal & lt), first = r0 + incl - n;
+    for (int k = 0; k < w; ++k) { pos += wp[k]; first += wr[k]; }
+    if (n > 0u) {
+        P.queue[pos] = q;
+        P.ray_base[pos] = first;
+    }
+    if (blockIdx.x == gridDim.x - 1 && tid == 0) {
+        P.counters[kCntMasked] = p0 + wp[0] + wp[1] + wp[2] + wp[3];
+        P.counters[kCntRays] = r0 + rays;
+    }
+    s_base[tid] = first;
+    for (uint32_t w0 = 0; w0 < rays; w0 += kSmallRays) {   // block-uniform
+        const uint32_t wn = rays - w0 < (uint32_t)kSmallRays ? rays - w0 : (uint32_t)kSmallRays;
+        const uint32_t k0 = first - r0;   // the pixel's rays within the window
+        for (uint32_t k = k0 > w0 ? k0 : w0; k < k0 + n && k < w0 + wn; ++k) s_pix[k - w0] = (uint8_t)tid;
+        __syncthreads();
+        for (uint32_t t = (uint32_t)tid; t < wn; t += kGenTB) {
+            const uint32_t px = s_pix[t], ray = r0 + w0 + t;
+            float o[3], d[3];
+            thin_lens_ray(fc, q0 + px, hw, hh, ray - s_base[px], o, d);
+            put_ray(P.rec0, P.rec1, ray, o, d);
+        }
+        __syncthreads();   // the window's map is rewritten
+    }
+}
+
 // Shading and resolve of a frame's lens rays in one pass: each block shades
 // the rays of its 64 pixels straight into the resolve's LDS chunks (and, when
 // the frame keeps them, into the per-ray planes), so nothing is read back.
@@ -1253,6 +1335,13 @@ hipError_t launch_trace(const SceneDev &s, const FrameConst &fc, const ScratchLa
                                                   reinterpret_cast<unsigned long long *>(cnt + kCntWork + kStatAt),
                                                   cnt + kCntWork + kStatAt + 4, fc.tk);
     });
+    return hipGetLastError();
+}
+
+hipError_t launch_compact_small(const FrameConst &fc, const ScratchLayout &L, char *scratch, const uint8_t *mask, hipStream_t st)
+{
+    const uint32_t np = (uint32_t)fc.hw * (uint32_t)fc.hh;
+    k_compact_small<<<(np + kGenTB - 1) / kGenTB, kGenTB, 0, st>>>(fc, planes(fc, L, scratch), mask);
     return hipGetLastError();
 }
 

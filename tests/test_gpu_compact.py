@@ -1,0 +1,57 @@
+"""The compaction of a frame's mask and its ray generation, which a small frame
+does in one launch: one block per 256 half-res pixels, rays of a block in
+windows of 4096, up to 131072 half-res pixels and for masks aligned to 4 bytes.
+Queue, first rays, counts and every ray's hit and distance equal the oracle's
+(exact), at those edges and either side of the largest size."""
+
+import dataclasses
+
+import numpy as np
+import pytest
+
+from paper_2210_06158_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env(orc):
+    from paper_2210_06158_amd import dof
+    scene, cam, lens, params = synth.scene_small()
+    osc = orc.OracleScene(scene)
+    osc.build_bvh()
+    gs = dof.Scene(scene)
+    gs.build_bvh()
+    return osc, gs, cam, lens, params
+
+
+# half-res pixels 1, 255, 256, 257 and 16 x 17; 362 x 362 = 131044 and 363 x 363 = 131769;
+# m 17 with every pixel masked: 4352 rays a block; offset 1: an unaligned mask
+@pytest.mark.parametrize("w,h,m,mode,blades,offset", [
+    (2, 2, 4, synth.MASK_ALL, 0, 0), (30, 34, 4, synth.MASK_ALL, 0, 0), (32, 32, 17, synth.MASK_ALL, 6, 0),
+    (2, 514, 255, synth.MASK_ALL, 0, 0), (32, 34, 16, synth.MASK_ADAPTIVE, 5, 0), (256, 256, 30, synth.MASK_ADAPTIVE, 0, 0),
+    (256, 256, 4, synth.MASK_ADAPTIVE, 0, 1), (724, 724, 2, synth.MASK_DILATE, 6, 0), (726, 726, 2, synth.MASK_DILATE, 0, 0)])
+def test_queue_and_rays(env, orc, w, h, m, mode, blades, offset):
+    import torch
+    from paper_2210_06158_amd import dof
+    osc, gs, cam, lens, params = env
+    cam = dataclasses.replace(cam, width=w, height=h)
+    lens = dataclasses.replace(lens, blades=blades)
+    p = dataclasses.replace(params, m=m, mask_mode=mode)
+    gb = orc.gbuffer(osc, cam, lens)
+    want = orc.render_frame(osc, cam, lens, p, gb)
+    print(f"{w}x{h} m {m} mode {mode} blades {blades} offset {offset}", flush=True)
+    fr = dof.Frame(w, h, p, ray_records=True)
+    if offset:
+        whole = torch.zeros(fr.mask.numel() + offset, dtype=torch.uint8, device="cuda")
+        fr.mask = whole[offset:].view(fr.mask.shape)
+    g = tuple(torch.from_numpy(x).cuda() for x in (gb.colour, gb.depth, gb.normal))
+    for _ in range(2):    # the second frame meets the first one's counters
+        fr.render(gs, cam, lens, g, None, dof.history_alloc(w, h))
+    torch.cuda.synchronize()
+    d = fr.debug()
+    assert np.array_equal(fr.mask.cpu().numpy(), want["mask"])
+    assert d["n_masked"] == want["n_masked"] and d["n_rays"] == want["n_rays"]
+    assert np.array_equal(d["queue"], want["queue"]) and np.array_equal(d["ray_base"], want["ray_base"])
+    assert np.array_equal(d["ray_hit"], want["ray_hit"])
+    assert np.array_equal(d["ray_t"].view(np.uint32), want["ray_t"].view(np.uint32))
