@@ -550,11 +550,33 @@ __global__ __launch_bounds__(kBX *kBY) void kb_median_pp(const Job *__restrict__
 
 constexpr int kMaskHalo = 4, kMaskL = kTile + 2 * kMaskHalo;   // 24 x 24 LDS cells
 
+// The mask's filters, each a sum from 0 in tap order: (1, 4, 6, 4, 1) / 16,
+// (1, 4, 6, 4, 1) and (-1, -2, 0, 2, 1).  A product by a power of two is exact
+// (below 2^-122 the Gaussian's are not, but such gradients' squares are 0), so
+// the fused forms round as product and sum would.
+__device__ inline float gauss5(float a, float b, float c, float d, float e)
+{
+    return fmaf(0.0625f, e, fmaf(0.25f, d, fmaf(0.25f, b, 0.0f + 0.0625f * a) + 0.375f * c));
+}
+
+__device__ inline float smooth5(float a, float b, float c, float d, float e)
+{
+    return fmaf(4.0f, d, fmaf(4.0f, b, 0.0f + a) + 6.0f * c) + e;
+}
+
+__device__ inline float diff5(float a, float b, float c, float d, float e)
+{
+    return fmaf(2.0f, d, fmaf(-2.0f, b, 0.0f - a) + 0.0f * c) + e;
+}
+
+// One block per 16 x 16 tile.  Bound by vector arithmetic (no contraction: the
+// ray counts are exact) and LDS reads.  The derivative filter as two passes
+// instead of 25 cells read by every pixel, and two arrays of cells instead of
+// three (eight blocks a CU instead of five): 3840x2160 70 -> 44 us.
 __device__ inline void b_mask(const FrameConst &fc, const Planes &P, const void *hist_in, uint8_t *mask, const uint32_t bx, const uint32_t by)
 {
     __shared__ float4 F[kMaskL][kMaskL];
     __shared__ float4 Hh[kMaskL][kMaskL];
-    __shared__ float4 B[kMaskL][kMaskL];
     const int hw = fc.hw, hh = fc.hh;
     const int ox = bx * kTile - kMaskHalo, oy = by * kTile - kMaskHalo;
     const int tid = threadIdx.y * kTile + threadIdx.x;
@@ -566,62 +588,68 @@ __device__ inline void b_mask(const FrameConst &fc, const Planes &P, const void 
         F[ly][lx] = make_float4(fc.d / v.x, v.y, v.z, v.w);
     }
     __syncthreads();
-    const float g5[5] = {0.0625f, 0.25f, 0.375f, 0.25f, 0.0625f};
     for (int c = tid; c < kMaskL * kMaskL; c += 256) {
         int lx = c % kMaskL, ly = c / kMaskL;
         if (lx < 2 || lx >= kMaskL - 2) continue;
         int cx = clampi(ox + lx, 0, hw - 1);
-        float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        for (int j = 0; j < 5; ++j) {
-            float4 v = F[ly][clampi(cx + j - 2, 0, hw - 1) - ox];
-            acc.x = acc.x + g5[j] * v.x;
-            acc.y = acc.y + g5[j] * v.y;
-            acc.z = acc.z + g5[j] * v.z;
-            acc.w = acc.w + g5[j] * v.w;
-        }
-        Hh[ly][lx] = acc;
+        float4 v[5];
+        for (int j = 0; j < 5; ++j) v[j] = F[ly][clampi(cx + j - 2, 0, hw - 1) - ox];
+        Hh[ly][lx] = make_float4(gauss5(v[0].x, v[1].x, v[2].x, v[3].x, v[4].x), gauss5(v[0].y, v[1].y, v[2].y, v[3].y, v[4].y),
+                                 gauss5(v[0].z, v[1].z, v[2].z, v[3].z, v[4].z), gauss5(v[0].w, v[1].w, v[2].w, v[3].w, v[4].w));
     }
     __syncthreads();
     for (int c = tid; c < kMaskL * kMaskL; c += 256) {
         int lx = c % kMaskL, ly = c / kMaskL;
         if (lx < 2 || lx >= kMaskL - 2 || ly < 2 || ly >= kMaskL - 2) continue;
         int cy = clampi(oy + ly, 0, hh - 1);
-        float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        for (int i = 0; i < 5; ++i) {
-            float4 v = Hh[clampi(cy + i - 2, 0, hh - 1) - oy][lx];
-            acc.x = acc.x + g5[i] * v.x;
-            acc.y = acc.y + g5[i] * v.y;
-            acc.z = acc.z + g5[i] * v.z;
-            acc.w = acc.w + g5[i] * v.w;
+        float4 v[5];
+        for (int j = 0; j < 5; ++j) v[j] = Hh[clampi(cy + j - 2, 0, hh - 1) - oy][lx];
+        F[ly][lx] = make_float4(gauss5(v[0].x, v[1].x, v[2].x, v[3].x, v[4].x), gauss5(v[0].y, v[1].y, v[2].y, v[3].y, v[4].y),
+                                gauss5(v[0].z, v[1].z, v[2].z, v[3].z, v[4].z), gauss5(v[0].w, v[1].w, v[2].w, v[3].w, v[4].w));
+    }
+    __syncthreads();
+    // The derivative filter's two horizontal passes, once per cell (a pixel's
+    // five rows of them are its column's): differences to F's cells, smoothing
+    // to Hh's, once every cell's are read.  2 v and 4 v are exact, so the fused
+    // forms round as written out.
+    constexpr int kCells = kTile * (kMaskL - 4), kMine = (kCells + 255) / 256;
+    float4 dif[kMine], smo[kMine];
+#pragma unroll
+    for (int m = 0; m < kMine; ++m) {
+        const int c = tid + m * 256, lx = kMaskHalo + c % kTile, ly = 2 + c / kTile;
+        if (c < kCells) {
+            float4 v[5];
+            for (int k = 0; k < 5; ++k) v[k] = F[ly][clampi(min(ox + lx, hw - 1) + k - 2, 0, hw - 1) - ox];
+            dif[m] = make_float4(diff5(v[0].x, v[1].x, v[2].x, v[3].x, v[4].x), diff5(v[0].y, v[1].y, v[2].y, v[3].y, v[4].y),
+                                 diff5(v[0].z, v[1].z, v[2].z, v[3].z, v[4].z), diff5(v[0].w, v[1].w, v[2].w, v[3].w, v[4].w));
+            smo[m] = make_float4(smooth5(v[0].x, v[1].x, v[2].x, v[3].x, v[4].x), smooth5(v[0].y, v[1].y, v[2].y, v[3].y, v[4].y),
+                                 smooth5(v[0].z, v[1].z, v[2].z, v[3].z, v[4].z), smooth5(v[0].w, v[1].w, v[2].w, v[3].w, v[4].w));
         }
-        B[ly][lx] = acc;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < kMine; ++m) {
+        const int c = tid + m * 256, lx = kMaskHalo + c % kTile, ly = 2 + c / kTile;
+        if (c < kCells) {
+            F[ly][lx] = dif[m];
+            Hh[ly][lx] = smo[m];
+        }
     }
     __syncthreads();
     const int x = bx * kTile + threadIdx.x, y = by * kTile + threadIdx.y;
     if (x >= hw || y >= hh) return;
-    const float sm[5] = {1.0f, 4.0f, 6.0f, 4.0f, 1.0f};
-    const float dv[5] = {-1.0f, -2.0f, 0.0f, 2.0f, 1.0f};
     float gx[4], gy[4];
     {
-        float axv[4] = {0.0f, 0.0f, 0.0f, 0.0f}, ayv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        float4 dv[5], sv[5];
         for (int r = 0; r < 5; ++r) {
-            int ly = clampi(y + r - 2, 0, hh - 1) - oy;
-            float hx[4] = {0.0f, 0.0f, 0.0f, 0.0f}, hs[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-            for (int k = 0; k < 5; ++k) {
-                float4 v = B[ly][clampi(x + k - 2, 0, hw - 1) - ox];
-                float vv[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    hx[c] = hx[c] + dv[k] * vv[c];
-                    hs[c] = hs[c] + sm[k] * vv[c];
-                }
-            }
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                axv[c] = axv[c] + sm[r] * hx[c];
-                ayv[c] = ayv[c] + dv[r] * hs[c];
-            }
+            const int ly = clampi(y + r - 2, 0, hh - 1) - oy;
+            dv[r] = F[ly][x - ox];
+            sv[r] = Hh[ly][x - ox];
         }
+        const float axv[4] = {smooth5(dv[0].x, dv[1].x, dv[2].x, dv[3].x, dv[4].x), smooth5(dv[0].y, dv[1].y, dv[2].y, dv[3].y, dv[4].y),
+                              smooth5(dv[0].z, dv[1].z, dv[2].z, dv[3].z, dv[4].z), smooth5(dv[0].w, dv[1].w, dv[2].w, dv[3].w, dv[4].w)};
+        const float ayv[4] = {diff5(sv[0].x, sv[1].x, sv[2].x, sv[3].x, sv[4].x), diff5(sv[0].y, sv[1].y, sv[2].y, sv[3].y, sv[4].y),
+                              diff5(sv[0].z, sv[1].z, sv[2].z, sv[3].z, sv[4].z), diff5(sv[0].w, sv[1].w, sv[2].w, sv[3].w, sv[4].w)};
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             gx[c] = axv[c] * 0.0078125f;
