@@ -310,10 +310,10 @@ __device__ inline int job_of_block(const Job *__restrict__ jobs, int njobs, int 
 
 // One wave per 64 consecutive queue entries.  Their rays are one contiguous
 // range (a pixel's rays follow each other in queue order), which the wave
-// stages into LDS in chunks: fill(c0, c1, col, pos, hit) writes rays
-// [c0, c1) (colour with view depth, hit position, hit id) with the 64 lanes
-// sharing the work; each lane then sums its pixel's rays from LDS in ray
-// order, as the single-thread loop would.
+// stages into LDS in chunks: fill(c0, c1, col, pos) writes rays [c0, c1)
+// (colour with CoC diameter, hit position with the near weight, or -1 for a
+// miss) with the 64 lanes sharing the work; each lane then sums its pixel's
+// rays from LDS in ray order, as the single-thread loop would.
 constexpr int kResolveChunk = 256;
 
 template <class Fill>
@@ -321,7 +321,6 @@ __device__ inline void resolve_block(const FrameConst &fc, const Planes &P, cons
                                      const uint32_t bx, Fill fill)
 {
     __shared__ float4 s_col[kResolveChunk], s_pos[kResolveChunk];
-    __shared__ int32_t s_hit[kResolveChunk];
     const uint32_t masked = P.counters[kCntMasked];
     const uint32_t j0 = bx * 64;
     if (j0 >= masked) return;
@@ -340,15 +339,13 @@ __device__ inline void resolve_block(const FrameConst &fc, const Planes &P, cons
     float scn = 0.0f, scf = 0.0f, fp0 = 0.0f, fp1 = 0.0f, fp2 = 0.0f, fw = 0.0f;
     for (uint32_t c0 = r0; c0 < r1; c0 += kResolveChunk) {
         const uint32_t c1 = min(c0 + (uint32_t)kResolveChunk, r1);
-        fill(c0, c1, s_col, s_pos, s_hit);
+        fill(c0, c1, s_col, s_pos);
         __syncthreads();
         const uint32_t kb = max(base, c0), ke = min(base + (uint32_t)n, c1);
         for (uint32_t r = kb; r < ke; ++r) {
-            const float4 c = s_col[r - c0];
-            const bool hit = s_hit[r - c0] >= 0;
-            float w = hit ? sat(0.5f + (fc.d - c.w) / fc.ramp) : 0.0f;
-            float om = 1.0f - w;
-            float cz = coc_px(fc.cock, fc.d, c.w);
+            const float4 c = s_col[r - c0], p = s_pos[r - c0];
+            const bool hit = p.w != -1.0f;
+            const float w = hit ? p.w : 0.0f, om = 1.0f - w, cz = c.w;
             N = N + w;
             sn0 = sn0 + w * c.x; sf0 = sf0 + om * c.x;
             sn1 = sn1 + w * c.y; sf1 = sf1 + om * c.y;
@@ -356,7 +353,6 @@ __device__ inline void resolve_block(const FrameConst &fc, const Planes &P, cons
             scn = scn + w * cz;
             scf = scf + om * cz;
             if (hit) {
-                const float4 p = s_pos[r - c0];
                 fp0 = fp0 + om * p.x;
                 fp1 = fp1 + om * p.y;
                 fp2 = fp2 + om * p.z;

@@ -223,11 +223,21 @@ struct Shaded {
     float n0, n1, n2;
 };
 
+// A leaf's triangle (its id in the first vertex's w) and albedo.
+struct LeafData {
+    float4 v0, v1, v2, al;
+};
+
+__device__ inline LeafData load_leaf(const SceneArgs &S, uint32_t leaf)
+{
+    return {S.tris[3 * (size_t)leaf], S.tris[3 * (size_t)leaf + 1], S.tris[3 * (size_t)leaf + 2], S.albedo[leaf]};
+}
+
 // Lambert: two-sided geometric normal facing the ray, one directional light
 // plus ambient.
-__device__ inline Shaded shade(const SceneArgs &S, const SceneShade &sh, uint32_t leaf, const float d[3])
+__device__ inline Shaded shade(const LeafData &leaf, const SceneShade &sh, const float d[3])
 {
-    float4 v0 = S.tris[3 * (size_t)leaf], v1 = S.tris[3 * (size_t)leaf + 1], v2 = S.tris[3 * (size_t)leaf + 2];
+    const float4 v0 = leaf.v0, v1 = leaf.v1, v2 = leaf.v2, al = leaf.al;
     float e10 = v1.x - v0.x, e11 = v1.y - v0.y, e12 = v1.z - v0.z;
     float e20 = v2.x - v0.x, e21 = v2.y - v0.y, e22 = v2.z - v0.z;
     float n0 = e11 * e22 - e12 * e21, n1 = e12 * e20 - e10 * e22, n2 = e10 * e21 - e11 * e20;
@@ -236,7 +246,6 @@ __device__ inline Shaded shade(const SceneArgs &S, const SceneShade &sh, uint32_
     if ((n0 * d[0] + n1 * d[1]) + n2 * d[2] > 0.0f) { n0 = -n0; n1 = -n1; n2 = -n2; }
     float ndl = -((n0 * sh.light_dir[0] + n1 * sh.light_dir[1]) + n2 * sh.light_dir[2]);
     if (!(ndl > 0.0f)) ndl = 0.0f;
-    float4 al = S.albedo[leaf];
     Shaded o;
     o.r = al.x * (sh.light_rad[0] * ndl + sh.ambient[0]);
     o.g = al.y * (sh.light_rad[1] * ndl + sh.ambient[1]);
@@ -357,20 +366,19 @@ __device__ inline void lens_ray(const FrameConst &fc, const uint32_t *queue, con
     thin_lens_ray(fc, queue[j], (uint32_t)fc.hw, (uint32_t)fc.hh, r - ray_base[j], o, d);
 }
 
-// Per-ray record of a lens ray: hit id, distance, shaded colour with view
-// depth, hit position (sky colour and +inf depth on a miss).
 // Hit id, distance, shaded colour with view depth and hit position of a lens
-// ray (sky colour and +inf depth on a miss).
-__device__ inline void lens_shade(const SceneArgs &S, const FrameConst &fc, const float o[3], const float d[3],
-                                  const Hit &h, int32_t &hit, float &t, float4 &col, float4 &pos)
+// ray whose traversal left (leaf, t) (sky colour and +inf depth on a miss, for
+// which data may be any leaf's).
+__device__ inline void lens_shade(const LeafData &data, const FrameConst &fc, const float o[3], const float d[3],
+                                  uint2 lt, int32_t &hit, float &t, float4 &col, float4 &pos)
 {
-    if (h.id != ~0u) {
-        float P0 = o[0] + h.t * d[0], P1 = o[1] + h.t * d[1], P2 = o[2] + h.t * d[2];
+    if (lt.x != ~0u) {
+        t = __uint_as_float(lt.y);
+        float P0 = o[0] + t * d[0], P1 = o[1] + t * d[1], P2 = o[2] + t * d[2];
         float z = ((P0 - fc.cur.pos[0]) * fc.cur.fwd[0] + (P1 - fc.cur.pos[1]) * fc.cur.fwd[1]) +
                   (P2 - fc.cur.pos[2]) * fc.cur.fwd[2];
-        Shaded s = dof::shade(S, fc.shade, h.leaf, d);
-        hit = (int32_t)h.id;
-        t = h.t;
+        Shaded s = dof::shade(data, fc.shade, d);
+        hit = (int32_t)__float_as_uint(data.v0.w);
         col = make_float4(s.r, s.g, s.b, z);
         pos = make_float4(P0, P1, P2, 0.0f);
     } else {
@@ -407,17 +415,6 @@ __device__ inline void get_ray(const float4 *rec0, const float2 *rec1, uint32_t 
 __device__ inline void put_lt(uint2 *lt, uint32_t r, const Hit &h)
 {
     lt[r] = make_uint2(h.id == ~0u ? ~0u : h.leaf, __float_as_uint(h.t));
-}
-
-// Origin, direction and closest hit of lens ray r, from its ray record and
-// its traversal result.
-__device__ inline void ray_of(const SceneArgs &S, const Planes &P, uint32_t r, float o[3], float d[3], Hit &h)
-{
-    const uint2 lt = P.ray_lt[r];
-    get_ray(P.rec0, P.rec1, r, o, d);
-    h.t = __uint_as_float(lt.y);
-    h.leaf = lt.x;
-    h.id = lt.x == ~0u ? ~0u : __float_as_uint(S.tris[3 * (size_t)lt.x].w);
 }
 
 struct LensRays {
@@ -522,7 +519,7 @@ __global__ __launch_bounds__(256) void k_gbuffer_shade(SceneArgs S, SceneShade s
         const float t = src.depth[p];
         const ViewConst &v = src.view;
         const float P0 = o[0] + t * d[0], P1 = o[1] + t * d[1], P2 = o[2] + t * d[2];
-        const Shaded s = dof::shade(S, sh, leaf, d);
+        const Shaded s = dof::shade(load_leaf(S, leaf), sh, d);
         st_rgba(colour, cfmt, p, make_float4(s.r, s.g, s.b, 1.0f));
         src.depth[p] = ((P0 - v.pos[0]) * v.fwd[0] + (P1 - v.pos[1]) * v.fwd[1]) + (P2 - v.pos[2]) * v.fwd[2];
         st_rgba(src.normal, nfmt, p, make_float4(s.n0, s.n1, s.n2, 0.0f));
@@ -583,14 +580,10 @@ __global__ __launch_bounds__(256) void k_ref_average(SceneArgs S, RefRays src, u
         float o[3], d[3];
         src.ray(r, o, d);
         const uint2 lt = src.lt[r];
-        Hit h;
-        h.t = __uint_as_float(lt.y);
-        h.leaf = lt.x;
-        h.id = lt.x == ~0u ? ~0u : __float_as_uint(S.tris[3 * (size_t)lt.x].w);
         int32_t hi;
         float t;
         float4 c, p;
-        lens_shade(S, src.fc, o, d, h, hi, t, c, p);
+        lens_shade(load_leaf(S, lt.x != ~0u ? lt.x : 0u), src.fc, o, d, lt, hi, t, c, p);
         acc0 += (double)c.x;
         acc1 += (double)c.y;
         acc2 += (double)c.z;
@@ -787,27 +780,48 @@ __global__ __launch_bounds__(kGenTB) void k_compact_small(FrameConst fc, Planes 
 // Shading and resolve of a frame's lens rays in one pass: each block shades
 // the rays of its 64 pixels straight into the resolve's LDS chunks (and, when
 // the frame keeps them, into the per-ray planes), so nothing is read back.
+// Bound by the latency of two loads that depend on each other, a ray's record
+// and then its triangle, so a lane has kShadeRays rays in flight: at 3840x2160,
+// beside the gather, 218 us a frame with one and 166 with two (four hold more
+// registers and slow the gather's blocks down by as much).
+constexpr int kShadeRays = 2;
+
 __device__ inline void shade_resolve_block(const SceneArgs &S, const FrameConst &fc, const Planes &P,
                                            const uint8_t *__restrict__ mask, uint32_t bx)
 {
-    resolve_block(fc, P, mask, bx, [&](uint32_t c0, uint32_t c1, float4 *col, float4 *pos, int32_t *hit) {
-        for (uint32_t r = c0 + threadIdx.x; r < c1; r += 64) {
-            float o[3], d[3];
-            Hit h;
-            ray_of(S, P, r, o, d, h);
-            int32_t hi;
-            float t;
-            float4 c, p;
-            lens_shade(S, fc, o, d, h, hi, t, c, p);
-            if (P.ray_hit) {   // per-ray planes kept for inspection (params.ray_records)
-                P.ray_hit[r] = hi;
-                P.ray_t[r] = t;
-                P.ray_col[r] = c;
-                P.ray_pos[r] = p;
+    resolve_block(fc, P, mask, bx, [&](uint32_t c0, uint32_t c1, float4 *col, float4 *pos) {
+        for (uint32_t b0 = c0 + threadIdx.x; b0 < c1; b0 += 64 * kShadeRays) {
+            // a ray past the end repeats the last one
+            uint2 lt[kShadeRays];
+            float o[kShadeRays][3], d[kShadeRays][3];
+            LeafData data[kShadeRays];
+#pragma unroll
+            for (int u = 0; u < kShadeRays; ++u) {
+                const uint32_t r = min(b0 + 64u * u, c1 - 1u);
+                lt[u] = P.ray_lt[r];
+                get_ray(P.rec0, P.rec1, r, o[u], d[u]);
             }
-            col[r - c0] = c;
-            pos[r - c0] = p;
-            hit[r - c0] = hi;
+#pragma unroll
+            for (int u = 0; u < kShadeRays; ++u) data[u] = load_leaf(S, lt[u].x != ~0u ? lt[u].x : 0u);
+#pragma unroll
+            for (int u = 0; u < kShadeRays; ++u) {
+                const uint32_t r = b0 + 64u * u;
+                if (r >= c1) break;
+                int32_t hi;
+                float t;
+                float4 c, p;
+                lens_shade(data[u], fc, o[u], d[u], lt[u], hi, t, c, p);
+                if (P.ray_hit) {   // per-ray planes kept for inspection (params.ray_records)
+                    P.ray_hit[r] = hi;
+                    P.ray_t[r] = t;
+                    P.ray_col[r] = c;
+                    P.ray_pos[r] = p;
+                }
+                p.w = hi >= 0 ? sat(0.5f + (fc.d - c.w) / fc.ramp) : -1.0f;
+                c.w = coc_px(fc.cock, fc.d, c.w);
+                col[r - c0] = c;
+                pos[r - c0] = p;
+            }
         }
     });
 }
