@@ -1306,7 +1306,11 @@ __device__ inline TapSums recon_taps(int q0, int q1, int x, int y, float Rr, flo
 static_assert(1 + 4 * kReconQuarter == kRingTaps && kReconQuarter % kReconTaps == 0, "whole quarters");
 
 constexpr int kReconSplit = 768;  // 16 x 16 tiles below which a frame's reconstruction takes 8 x 8 ones
-constexpr int kReconLds = 2368;   // mip texels a block can stage in LDS (37 KB: 4 blocks per CU)
+// Mip texels that a block can stage in LDS (24 KB: six blocks a CU, so that
+// blocks with few live pixels do not hold the others' place).  1200 leave too
+// many of 3840x2160's blocks to global memory (2204 us a frame against 2156),
+// 2368 let in four blocks a CU (2166; 1920x1080 443 against 437).
+constexpr int kReconLds = 1520;
 
 // Index range that the bilinear lookups of taps between coordinates lo and hi
 // (one axis, already at the level's scale sc) reach after the clamp to
