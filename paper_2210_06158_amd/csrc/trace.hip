@@ -857,6 +857,12 @@ constexpr int kShareSteps = 4;   // most node visits per lane between two shares
 // visits a million of them take 388 us instead of 377; four in every case take
 // 22 us for a thousand instead of 20.
 constexpr int kShareBusy = 48;
+// Rays per wave below which a small launch uses fewer waves: the waves of a
+// SIMD share its issue slots, and work sharing spreads a wave's rays over its
+// lanes.  With 4 a wave 1000 random rays take 19.5 us (8: 20.4, 16: 21.6), a
+// 256x256 frame 95 (3: 99, 8: 94), a 224x218 one among 319000 triangles 150
+// (8: 153, 16: 177), a 256x256 view 30.6 (3: 31.3, 16: 30.4).
+constexpr int kMinRays = 4;
 constexpr int kDropChunk = 8;    // oldest stack entries dropped when the LDS stack is full
 // Launch knobs (TraceKnobs, defaults in brackets): a wave refills when at
 // least tk.refill lanes are idle [16], takes tk.grab rays from the work
@@ -1018,7 +1024,8 @@ void k_traverse(SceneArgs S, Src src, uint32_t count, const uint32_t *count_ptr,
     };
 
     // A launch with no more rays than lanes deals them evenly over its waves,
-    // without counters.  A larger one gives every wave a first run and hands
+    // without counters, and leaves waves idle rather than give each fewer than
+    // so many.  A larger one gives every wave a first run and hands
     // out the others through the counters: run g of those is the k-th of
     // counter g mod parts, and a wave whose counter is past the last run takes
     // no more.  Takes are few because they are dear, one address taking an
@@ -1028,8 +1035,9 @@ void k_traverse(SceneArgs S, Src src, uint32_t count, const uint32_t *count_ptr,
     const uint32_t wave = blockIdx.x * (kTB / 64) + (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6), waves = gridDim.x * (kTB / 64);
     const uint32_t parts = min((uint32_t)kWorkParts, gridDim.x), part = blockIdx.x % parts;
     if (N <= gridDim.x * (uint32_t)kTB) {
-        pool = (uint32_t)((uint64_t)N * wave / waves);
-        pool_end = (uint32_t)((uint64_t)N * (wave + 1) / waves);
+        const uint32_t used = max(1u, min(waves, N / (uint32_t)kMinRays));
+        pool = wave < used ? (uint32_t)((uint64_t)N * wave / used) : N;
+        pool_end = wave < used ? (uint32_t)((uint64_t)N * (wave + 1) / used) : N;
         drained = true;
     } else {
         const uint64_t b = (uint64_t)wave * grab;
@@ -1322,11 +1330,7 @@ void with_default(int32_t nleaf, F f)
 }
 
 // A traversal of few rays needs no more blocks than give each wave kMinRays
-// of them: they spread over the chip, and work sharing spreads each over its
-// wave (1000 rays: 21.1, 21.2, 22.0, 22.9 us at 1, 2, 4, 8 rays per wave, but
-// a 256 x 256 view is no slower at 16, so the line saves launching blocks).
-constexpr int kMinRays = 4;
-
+// of them.
 int blocks_for(int blocks, int64_t rays)
 {
     const int64_t per = (int64_t)kMinRays * (kTB / 64), need = (rays + per - 1) / per;
