@@ -179,7 +179,6 @@ dof::ScratchLayout frame_layout(int W, int H, int m, int taa, int ray_records)
     L.prev_idx = take(4 * np);
     L.mask_raw = take(np);
     L.chunk_cnt = take(8 * (size_t)L.nchunks);
-    L.chunk_off = take(8 * (size_t)L.nchunks);
     L.counters = take(dof::kCountersBytes);
     L.queue = take(4 * np);
     L.ray_base = take(4 * np);

@@ -134,7 +134,7 @@ struct FrameConst {
 // Byte offsets of every plane in a frame's scratch buffer.
 struct ScratchLayout {
     size_t colr, zn, zh, tile_max, tile_dil, pre, gather, ppmed, prev_idx, mask_raw;
-    size_t chunk_cnt, chunk_off, counters;
+    size_t chunk_cnt, counters;
     size_t queue, ray_base, ray_pix, ray_rec, ray_lt, ray_hit, ray_t, ray_col, ray_pos;
     size_t gtex, resolve, temporal, var_blur, rtmed, mips, tap, recon, comp, rast, pptaa;
     size_t total;
@@ -149,7 +149,7 @@ struct Planes {
     float4 *colr, *zn, *pre, *gather, *ppmed;
     float *zh, *tile_max, *tile_dil;
     int32_t *prev_idx;
-    uint2 *chunk_cnt, *chunk_off;
+    uint2 *chunk_cnt;
     uint32_t *counters, *queue, *ray_base, *ray_pix;
     int32_t *ray_hit;        // per-ray planes: nullptr unless params.ray_records
     float *ray_t;

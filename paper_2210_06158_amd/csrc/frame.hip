@@ -166,7 +166,6 @@ Planes planes(const FrameConst &fc, const ScratchLayout &L, char *s)
     p.ppmed = reinterpret_cast<float4 *>(s + L.ppmed);
     p.prev_idx = reinterpret_cast<int32_t *>(s + L.prev_idx);
     p.chunk_cnt = reinterpret_cast<uint2 *>(s + L.chunk_cnt);
-    p.chunk_off = reinterpret_cast<uint2 *>(s + L.chunk_off);
     p.counters = reinterpret_cast<uint32_t *>(s + L.counters);
     p.queue = reinterpret_cast<uint32_t *>(s + L.queue);
     p.ray_base = reinterpret_cast<uint32_t *>(s + L.ray_base);
@@ -893,50 +892,8 @@ __global__ __launch_bounds__(256) void kb_compact_count(const Job *__restrict__ 
 {
     uint32_t bx, by;
     const Job &J = jobs[job_of_block(jobs, njobs, kGridChunk, blockIdx.x, bx, by)];
+    if (bx == 0 && threadIdx.x == 0) J.P.counters[kCntWild] = 0u;
     b_compact_count((int64_t)J.fc.hw * J.fc.hh, J.mask, J.P, bx, by);
-}
-
-__device__ inline void b_compact_scan(int64_t nchunks, const Planes &P)
-{
-    __shared__ uint32_t pp[1024], pr[1024];
-    const int per = (int)((nchunks + 1023) / 1024);
-    const int b = threadIdx.x * per, e = (int)min((int64_t)(b + per), nchunks);
-    uint32_t sp = 0, sr = 0;
-    for (int i = b; i < e; ++i) {
-        uint2 c = P.chunk_cnt[i];
-        sp += c.x;
-        sr += c.y;
-    }
-    pp[threadIdx.x] = sp;
-    pr[threadIdx.x] = sr;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        uint32_t a = threadIdx.x >= (unsigned)off ? pp[threadIdx.x - off] : 0u;
-        uint32_t c = threadIdx.x >= (unsigned)off ? pr[threadIdx.x - off] : 0u;
-        __syncthreads();
-        pp[threadIdx.x] += a;
-        pr[threadIdx.x] += c;
-        __syncthreads();
-    }
-    uint32_t rp = pp[threadIdx.x] - sp, rr = pr[threadIdx.x] - sr;
-    for (int i = b; i < e; ++i) {
-        uint2 c = P.chunk_cnt[i];
-        P.chunk_off[i] = make_uint2(rp, rr);
-        rp += c.x;
-        rr += c.y;
-    }
-    if (threadIdx.x == 1023) {
-        P.counters[kCntMasked] = pp[1023];
-        P.counters[kCntRays] = pr[1023];
-        P.counters[kCntWild] = 0u;
-    }
-}
-
-__global__ __launch_bounds__(1024) void kb_compact_scan(const Job *__restrict__ jobs)
-{
-    const Job &J = jobs[blockIdx.x];
-    const int64_t np = (int64_t)J.fc.hw * J.fc.hh;
-    b_compact_scan((np + kChunk - 1) / kChunk, J.P);
 }
 
 __device__ inline void b_compact_scatter(int64_t np, const uint8_t *__restrict__ mask, const Planes &P, const uint32_t bx,
@@ -988,14 +945,13 @@ __device__ inline void b_compact_scatter(int64_t np, const uint8_t *__restrict__
     }
 }
 
-// A frame's scatter finds its chunk's offsets itself, summing the counts of
-// the chunks before it (integer sums: the same offsets as a scan), so a
-// frame needs no separate scan launch; the last chunk's block writes the
-// totals.
-__global__ __launch_bounds__(256) void k_compact_scatter(int64_t np, const uint8_t *__restrict__ mask, Planes P)
+// The scatter finds its chunk's offsets itself, summing the counts of the
+// chunks before it (whole numbers: the same offsets as a scan), so there is no
+// scan launch; the last chunk's block writes the totals.
+__device__ inline void b_scatter_chunk(int64_t np, const uint8_t *__restrict__ mask, const Planes &P, const uint32_t bx,
+                                       const uint32_t by, const uint32_t nchunks)
 {
     __shared__ uint32_t sp[4], sr[4];
-    const uint32_t bx = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     uint32_t cp = 0, cr = 0;
     for (uint32_t i = (uint32_t)tid; i < bx; i += 256) {
@@ -1010,19 +966,25 @@ __global__ __launch_bounds__(256) void k_compact_scatter(int64_t np, const uint8
     if (lane == 0) { sp[w] = cp; sr[w] = cr; }
     __syncthreads();
     const uint2 start = make_uint2(sp[0] + sp[1] + sp[2] + sp[3], sr[0] + sr[1] + sr[2] + sr[3]);
-    if (bx == gridDim.x - 1 && tid == 0) {
+    if (bx == nchunks - 1 && tid == 0) {
         const uint2 c = P.chunk_cnt[bx];
         P.counters[kCntMasked] = start.x + c.x;
         P.counters[kCntRays] = start.y + c.y;
     }
-    b_compact_scatter(np, mask, P, bx, blockIdx.y, start);
+    b_compact_scatter(np, mask, P, bx, by, start);
+}
+
+__global__ __launch_bounds__(256) void k_compact_scatter(int64_t np, const uint8_t *__restrict__ mask, Planes P)
+{
+    b_scatter_chunk(np, mask, P, blockIdx.x, blockIdx.y, gridDim.x);
 }
 
 __global__ __launch_bounds__(256) void kb_compact_scatter(const Job *__restrict__ jobs, int njobs)
 {
     uint32_t bx, by;
     const Job &J = jobs[job_of_block(jobs, njobs, kGridChunk, blockIdx.x, bx, by)];
-    b_compact_scatter((int64_t)J.fc.hw * J.fc.hh, J.mask, J.P, bx, by, J.P.chunk_off[bx]);
+    const int64_t np = (int64_t)J.fc.hw * J.fc.hh;
+    b_scatter_chunk(np, J.mask, J.P, bx, by, (uint32_t)((np + kChunk - 1) / kChunk));
 }
 
 // ---------------------------------------------------------------- A11
@@ -1706,36 +1668,33 @@ __global__ __launch_bounds__(kBX *kBY) void k_composite(FrameConst fc, Planes P,
     b_composite(fc, P, gb, out, blockIdx.x, blockIdx.y);
 }
 
-__global__ __launch_bounds__(kBX *kBY) void kb_composite(const Job *__restrict__ jobs, int njobs)
+// Also, with an item's first thread, its stats record: masked pixels and rays
+// (the traversal's statistics of a batch are kept once, in its head, where the
+// first item's sums the slots).
+__global__ __launch_bounds__(kBX *kBY) void kb_composite(BatchHead *head, const Job *__restrict__ jobs, int njobs)
 {
     uint32_t bx, by;
-    const Job &J = jobs[job_of_block(jobs, njobs, kGridFull, blockIdx.x, bx, by)];
-    b_composite(J.fc, J.P, J.gb, J.out, bx, by);
-}
-
-// Per-job stats records of a batch: masked pixels and rays of the job; the
-// traversal statistics of a batch are kept once, in its head (the first
-// thread sums the traversal's statistics slots there).
-__global__ void kb_stats(BatchHead *head, const Job *__restrict__ jobs, int njobs)
-{
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j == 0) {
-        unsigned long long v = 0ull, t = 0ull;
-        for (int p = 0; p < kWorkParts; ++p) {
-            const uint32_t *w = head->work + p * kWorkStride + kStatAt;
-            v += *reinterpret_cast<const unsigned long long *>(w);
-            t += *reinterpret_cast<const unsigned long long *>(w + 2);
+    const int j = job_of_block(jobs, njobs, kGridFull, blockIdx.x, bx, by);
+    const Job &J = jobs[j];
+    if (bx == 0 && by == 0 && threadIdx.x == 0 && threadIdx.y == 0) {
+        if (j == 0) {
+            unsigned long long v = 0ull, t = 0ull;
+            for (int p = 0; p < kWorkParts; ++p) {
+                const uint32_t *w = head->work + p * kWorkStride + kStatAt;
+                v += *reinterpret_cast<const unsigned long long *>(w);
+                t += *reinterpret_cast<const unsigned long long *>(w + 2);
+            }
+            head->visits = v;
+            head->tests = t;
         }
-        head->visits = v;
-        head->tests = t;
+        if (dof_stats *o = J.out.stats) {
+            o->masked_px = J.P.counters[kCntMasked];
+            o->rays = J.P.counters[kCntRays];
+            o->node_visits = 0;
+            o->tri_tests = 0;
+        }
     }
-    if (j >= njobs || !jobs[j].out.stats) return;
-    const uint32_t *c = jobs[j].P.counters;
-    dof_stats *o = jobs[j].out.stats;
-    o->masked_px = c[kCntMasked];
-    o->rays = c[kCntRays];
-    o->node_visits = 0;
-    o->tri_tests = 0;
+    b_composite(J.fc, J.P, J.gb, J.out, bx, by);
 }
 
 // ---------------------------------------------------------------- TAA
@@ -2046,7 +2005,6 @@ hipError_t launch_batch_pre(const BatchHead *, const Job *jobs, int njobs, const
     kb_mask<<<nblk[kGridTiles], dim3(kTile, kTile), 0, st>>>(jobs, njobs);
     if (dilate) kb_mask_dilate<<<nblk[kGridTiles], dim3(kTile, kTile), 0, st>>>(jobs, njobs);
     kb_compact_count<<<nblk[kGridChunk], 256, 0, st>>>(jobs, njobs);
-    kb_compact_scan<<<njobs, 1024, 0, st>>>(jobs);
     kb_compact_scatter<<<nblk[kGridChunk], 256, 0, st>>>(jobs, njobs);
     return hipGetLastError();
 }
@@ -2065,9 +2023,8 @@ hipError_t launch_batch_post(BatchHead *head, const Job *jobs, int njobs, const 
         const hipError_t e = hipStreamWaitEvent(st, side->join, 0);   // the post-process chain is done
         if (e != hipSuccess) return e;
     }
-    kb_composite<<<nblk[kGridFull], dim3(kBX, kBY), 0, st>>>(jobs, njobs);
+    kb_composite<<<nblk[kGridFull], dim3(kBX, kBY), 0, st>>>(head, jobs, njobs);
     if (taa & DOF_TAA_FINAL) kb_taa_final<<<nblk[kGridFull], dim3(kBX, kBY), 0, st>>>(jobs, njobs);
-    kb_stats<<<(njobs + 127) / 128, 128, 0, st>>>(head, jobs, njobs);
     return hipGetLastError();
 }
 

@@ -1275,23 +1275,32 @@ __global__ void k_zero_work(uint32_t *work)
 
 // First ray of every job of a batch (exclusive prefix of the jobs' ray
 // counts), the batch total, and cleared traversal counters.
-__global__ void kb_ray_offsets(BatchHead *head, const Job *__restrict__ jobs, int njobs)
+__global__ __launch_bounds__(64) void kb_ray_offsets(BatchHead *head, const Job *__restrict__ jobs, int njobs)
 {
-    if (threadIdx.x != 0) return;
+    const int lane = threadIdx.x;
     uint32_t acc = 0;
-    for (int j = 0; j < njobs; ++j) {
-        head->ray_off[j] = acc;
-        acc += jobs[j].P.counters[kCntRays];
+    for (int j0 = 0; j0 < njobs; j0 += 64) {
+        const int j = j0 + lane;
+        const uint32_t n = j < njobs ? jobs[j].P.counters[kCntRays] : 0u;
+        uint32_t incl = n;
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t u = __shfl_up(incl, o);
+            if (lane >= o) incl += u;
+        }
+        if (j < njobs) head->ray_off[j] = acc + incl - n;
+        acc += __shfl(incl, 63);
     }
-    head->ray_off[njobs] = acc;
-    head->rays = acc;
-    for (int p = 0; p < kWorkParts; ++p) {
-        uint32_t *w = head->work + p * kWorkStride;
+    if (lane < kWorkParts) {
+        uint32_t *w = head->work + lane * kWorkStride;
         w[0] = 0u;
         for (int k = 0; k < kStatWords; ++k) w[kStatAt + k] = 0u;
     }
-    head->visits = 0ull;
-    head->tests = 0ull;
+    if (lane == 0) {
+        head->ray_off[njobs] = acc;
+        head->rays = acc;
+        head->visits = 0ull;
+        head->tests = 0ull;
+    }
 }
 
 int clamp_blocks(int blocks) { return blocks < 1 ? 1 : (blocks > kMaxTraceBlocks ? kMaxTraceBlocks : blocks); }
