@@ -125,6 +125,25 @@ def test_batch_equals_single_frames(sess):
     assert rays > 0
 
 
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 127, 128])
+def test_batch_of_many_items_equals_single_frames(sess, n):
+    """A wave sums the items' rays 64 items at a time: counts about one and
+    two waves, up to the largest batch; every item bit-equal to its frame
+    rendered alone."""
+    torch, dof = sess["torch"], sess["dof"]
+    alone = render_alone(sess)
+    many = dict(sess, items=[sess["items"][k % len(alone)] for k in range(n)])
+    frs, houts = make_frames(many)
+    b = dof.Batch(n, sess["params"], ray_records=True)
+    b.set(batch_items(many, frs, houts))
+    b.run()
+    torch.cuda.synchronize()
+    for k in range(n):
+        same(grab(torch, frs[k], houts[k]), alone[k % len(alone)], f"item {k} of {n}")
+    nf, rays, _, _ = b.totals()
+    assert nf == n and rays == sum(alone[k % len(alone)]["n_rays"] for k in range(n))
+
+
 def test_batch_with_dilated_mask_equals_single_frames(sess):
     """Mask mode DOF_MASK_DILATE (an extra kernel between mask and
     compaction), batched vs alone."""
