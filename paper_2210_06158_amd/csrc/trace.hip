@@ -1260,7 +1260,7 @@ void k_traverse(SceneArgs S, Src src, uint32_t count, const uint32_t *count_ptr,
             v += __shfl_xor(v, off);
             t += __shfl_xor(t, off);
         }
-        if (lane == 0 && v) {
+        if (lane == 0 && (v | t) != 0ull) {   // a scene of one leaf has tests and no nodes
             unsigned long long *slot = stats + (blockIdx.x % kWorkParts) * (kWorkStride / 2);
             atomicAdd(slot, v);
             atomicAdd(slot + 1, t);

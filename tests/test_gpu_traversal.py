@@ -76,3 +76,33 @@ def test_every_run_is_handed_out(orc, blocks, grab):
     assert d["n_rays"] == want["n_rays"] > 128 * blocks
     assert np.array_equal(d["ray_hit"], want["ray_hit"])
     assert np.array_equal(d["ray_t"].view(np.uint32), want["ray_t"].view(np.uint32))
+
+
+@pytest.mark.parametrize("batch", [False, True])
+@pytest.mark.parametrize("leaf_batch", [0, 1])
+def test_counters_of_a_scene_of_one_leaf(batch, leaf_batch):
+    """No node to visit and one triangle test a ray (exact)."""
+    import dataclasses
+    import torch
+    from paper_2210_06158_amd import dof
+    scene, cam, lens, params = synth.scene_small()
+    scene = dataclasses.replace(scene, verts=scene.verts[:1], albedo=scene.albedo[:1], leaf_split=0)
+    cam = dataclasses.replace(cam, width=66, height=50)
+    params = dataclasses.replace(params, mask_mode=synth.MASK_ALL, m=5)
+    gs = dof.Scene(scene)
+    gs.build_bvh()
+    g = gs.render_gbuffer(cam, lens)
+    fr = dof.Frame(66, 50, params, knobs={"trace_leaf_batch": leaf_batch} if leaf_batch else None)
+    hist = dof.history_alloc(66, 50)
+    print(f"batch {batch} leaf batch {leaf_batch}", flush=True)
+    if batch:
+        b = dof.Batch(1, params, knobs={"trace_leaf_batch": leaf_batch} if leaf_batch else None)
+        b.set([fr.item(gs, cam, lens, g, None, hist)])
+        b.run()
+        _, rays, visits, tests = b.totals()
+    else:
+        fr.render(gs, cam, lens, g, None, hist)
+        torch.cuda.synchronize()
+        w = fr.stats.cpu().numpy().view(np.uint32)
+        rays, (visits, tests) = int(w[1]), (int(x) for x in w[2:6].view(np.uint64))
+    assert (rays, visits, tests) == (33 * 25 * 5, 0, 33 * 25 * 5)
