@@ -1447,10 +1447,13 @@ __device__ inline void b_recon(const FrameConst &fc, const Rings &rings, const P
             float e[4] = {INFINITY, INFINITY, INFINITY, INFINITY};
             if (__ballot(L0 == L) != 0ull) {
                 if (L0 == L) {
-                    e[0] = (float)x + (-Rr);
-                    e[1] = -((float)x + Rr);
-                    e[2] = (float)y + (-Rr);
-                    e[3] = -((float)y + Rr);
+                    // a radius that is no number counts as 0: its taps are
+                    // clamped into the box too, which must not be empty
+                    const float R = Rr == Rr ? Rr : 0.0f;
+                    e[0] = (float)x + (-R);
+                    e[1] = -((float)x + R);
+                    e[2] = (float)y + (-R);
+                    e[3] = -((float)y + R);
                 }
 #pragma unroll
                 for (int k = 0; k < 4; ++k) e[k] = wave_fmin(e[k]);

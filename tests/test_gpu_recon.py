@@ -68,3 +68,32 @@ def test_either_tile(envs, orc, w, h):
     o, d = run_pair(env, orc, cam, lens, params, gb)
     np.testing.assert_allclose(d["rtmed"], o["rtmed"], rtol=1e-5, atol=1e-5)
     np.testing.assert_allclose(d["recon"], o["recon"], rtol=1e-5, atol=1e-5)
+
+
+# one tile of either kind, and ragged ones
+@pytest.mark.parametrize("w,h", [(32, 32), (38, 34), (896, 896)])
+def test_circle_of_confusion_that_is_no_number(envs, w, h):
+    """A history whose CoC is infinite gives pixels whose CoC is NaN, here all
+    of a tile: no tap counts there, so the pixel is the median with its own
+    hit ratio, bit for bit (exact)."""
+    import torch
+    from paper_2210_06158_amd import dof
+    env, cam, lens, params = envs[1.0]
+    cam = dataclasses.replace(cam, width=w, height=h)
+    p = dataclasses.replace(params, mask_mode=synth.MASK_ALL, var_recon_w=2.0)
+    gs = env["gs"]
+    print(f"{w}x{h}", flush=True)
+    g = gs.render_gbuffer(cam, lens)
+    fr = dof.Frame(w, h, p, ray_records=True)
+    hist = [dof.history_alloc(w, h), dof.history_alloc(w, h)]
+    fr.render(gs, cam, lens, g, None, hist[0])
+    n = (w // 2) * (h // 2)
+    hist[0][8 * n:12 * n].view(n, 4).copy_(torch.tensor([np.inf, np.inf, 0.0, 1.0]))   # near and far CoC, luma mean and moment
+    cam1 = dataclasses.replace(cam, frame=1)
+    fr.render(gs, cam1, lens, g, hist[0], hist[1], prev_cam=cam, prev_lens=lens)
+    torch.cuda.synchronize()
+    d = fr.debug()
+    t1, med, rec = d["temporal"][1], d["rtmed"].reshape(d["recon"].shape), d["recon"]
+    nan = np.isnan(t1[..., 0])
+    assert nan[:16, :16].all() and (d["var_blur"].reshape(nan.shape)[:16, :16] > 0).all()
+    assert np.array_equal(rec[nan][:, :3], med[nan][:, :3]) and np.array_equal(rec[nan][:, 3], t1[nan][:, 1])
