@@ -5,6 +5,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <new>
 #include <vector>
 
@@ -400,7 +401,10 @@ void fill_frame_const(const dof_scene *s, const dof_camera &cam, const dof_lens 
     fc.T = p.tile;
     fc.tw = (fc.hw + fc.T - 1) / fc.T;
     fc.th = (fc.hh + fc.T - 1) / fc.T;
-    fc.D = (int)ceilf(p.r_max / (float)fc.T);
+    // no further than the grid reaches; a radius past the integers (infinity
+    // among them) has none: the neighbourhood is empty and its maximum 0
+    const float reach = ceilf(p.r_max / (float)fc.T);
+    fc.D = reach < 2147483648.0f ? std::min((int)reach, std::max(fc.tw, fc.th)) : -1;
     fc.m = p.m;
     fc.mask_mode = p.mask_mode;
     fc.taa = p.taa;

@@ -331,7 +331,8 @@ __device__ inline void b_prefilter(const FrameConst &fc, const Planes &P, bool d
             const int i0 = max((int)bx - fc.D, 0), i1 = min((int)bx + fc.D, fc.tw - 1);
             const int j0 = max((int)by - fc.D, 0), j1 = min((int)by + fc.D, fc.th - 1), w = i1 - i0 + 1;
             float m = 0.0f;
-            for (int e = tid; e < w * (j1 - j0 + 1); e += 64) m = fmax_cs(m, P.tile_max[(size_t)(j0 + e / w) * fc.tw + i0 + e % w]);
+            const int cells = fc.D >= 0 ? w * (j1 - j0 + 1) : 0;
+            for (int e = tid; e < cells; e += 64) m = fmax_cs(m, P.tile_max[(size_t)(j0 + e / w) * fc.tw + i0 + e % w]);
             for (int o = 32; o >= 1; o >>= 1) m = fmax_cs(m, __shfl_xor(m, o));
             if (tid == 0) {
                 s_rn = m;
@@ -351,7 +352,9 @@ __device__ inline void b_prefilter(const FrameConst &fc, const Planes &P, bool d
     const int bx0 = tap_axis((float)x0 - sp, hw).a, bx1 = tap_axis((float)wx + sp, hw).b;
     const int by0 = tap_axis((float)y0 - sp, hh).a, by1 = tap_axis((float)wy + sp, hh).b;
     const int bw = bx1 - bx0 + 1;
-    const bool staged = bw <= 28 && by1 - by0 + 1 <= 28;
+    // (while the coordinates are integers' too: a spacing of 2^31 wraps the
+    // second texel's index round to the first)
+    const bool staged = sp < 1073741824.0f && bw <= 28 && by1 - by0 + 1 <= 28;
     if (staged) {
         // 32 columns (28 at most in use) by 8 rows at a time
         const int c = tid & 31;
