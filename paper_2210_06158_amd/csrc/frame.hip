@@ -644,9 +644,10 @@ __global__ __launch_bounds__(kBX *kBY) void kb_median_pp(const Job *__restrict__
 constexpr int kMaskHalo = 4, kMaskL = kTile + 2 * kMaskHalo;   // 24 x 24 LDS cells
 
 // The mask's filters, each a sum from 0 in tap order: (1, 4, 6, 4, 1) / 16,
-// (1, 4, 6, 4, 1) and (-1, -2, 0, 2, 1).  A product by a power of two is exact
-// (below 2^-122 the Gaussian's are not, but such gradients' squares are 0), so
-// the fused forms round as product and sum would.
+// (1, 4, 6, 4, 1) and (-1, -2, 0, 2, 1).  A product by 1/16 or 1/4 is exact
+// (below 2^-122 it is not, but such gradients' squares are 0), so the fused
+// form rounds as product and sum would; 2 v and 4 v can overflow (the disparity
+// of a depth below 2^-126 of the focus distance), which a fused step would hide.
 __device__ inline float gauss5(float a, float b, float c, float d, float e)
 {
     return fmaf(0.0625f, e, fmaf(0.25f, d, fmaf(0.25f, b, 0.0f + 0.0625f * a) + 0.375f * c));
@@ -654,12 +655,12 @@ __device__ inline float gauss5(float a, float b, float c, float d, float e)
 
 __device__ inline float smooth5(float a, float b, float c, float d, float e)
 {
-    return fmaf(4.0f, d, fmaf(4.0f, b, 0.0f + a) + 6.0f * c) + e;
+    return ((((0.0f + a) + 4.0f * b) + 6.0f * c) + 4.0f * d) + e;
 }
 
 __device__ inline float diff5(float a, float b, float c, float d, float e)
 {
-    return fmaf(2.0f, d, fmaf(-2.0f, b, 0.0f - a) + 0.0f * c) + e;
+    return ((((0.0f - a) - 2.0f * b) + 0.0f * c) + 2.0f * d) + e;
 }
 
 // One block per 16 x 16 tile.  Bound by vector arithmetic (no contraction: the
@@ -703,8 +704,7 @@ __device__ inline void b_mask(const FrameConst &fc, const Planes &P, const void 
     __syncthreads();
     // The derivative filter's two horizontal passes, once per cell (a pixel's
     // five rows of them are its column's): differences to F's cells, smoothing
-    // to Hh's, once every cell's are read.  2 v and 4 v are exact, so the fused
-    // forms round as written out.
+    // to Hh's, once every cell's are read.
     constexpr int kCells = kTile * (kMaskL - 4), kMine = (kCells + 255) / 256;
     float4 dif[kMine], smo[kMine];
 #pragma unroll
