@@ -917,8 +917,9 @@ void k_traverse(SceneArgs S, Src src, uint32_t count, const uint32_t *count_ptr,
     // seven waves still fit the LDS); with 12 entries a 1080p frame dropped so
     // often that it took 797 instead of 508 us.
     constexpr int kRows = kStack == 16 ? kStack + kSteps : kStack;
-    // row 0 stays unused: an empty stack's top
-    __shared__ uint32_t lds_stack[(kRows + 1) * kTB];
+    // row 0 stays unused: an empty stack's top; the work sharing keeps 64-bit
+    // words in two of the rows
+    __shared__ alignas(16) uint32_t lds_stack[(kRows + 1) * kTB];
     const uint32_t grab = tk.grab;
     const int tid = threadIdx.x, lane = tid & 63;
     const uint32_t N = count_ptr ? *count_ptr : count;
