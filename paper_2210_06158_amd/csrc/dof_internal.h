@@ -141,7 +141,7 @@ struct ScratchLayout {
     int64_t nchunks;
 };
 
-constexpr int kSmallFrame = 1 << 17;   // half-res pixels up to which one launch compacts the mask and generates the rays
+constexpr int kSmallFrame = 1 << 17;   // half-res pixels up to which one launch may compact the mask and generate the rays
 constexpr int kChunk = 1024;   // pixels per compaction chunk (256 threads x 4)
 
 // Device pointers of every plane of one frame (from its scratch layout).

@@ -1871,6 +1871,30 @@ __global__ void k_fill_zero(float *p, int64_t n)
 
 inline dim3 grid2(int w, int h, int bx, int by) { return dim3((w + bx - 1) / bx, (h + by - 1) / by); }
 
+// Where one launch for the compaction and the ray generation is the faster
+// way.  It saves two launches, 5 to 9 us, but a block then makes all rays of
+// its 256 pixels, on at most 512 blocks where the general path has 2048, and a
+// bladed aperture's without the general path's second pass for rays whose first
+// tries fail.  Its frame's time against the general path's, at 128x128,
+// 256x256, 512x512 and 724x724 (866 triangles, us):
+//   circle, m 30, every pixel    178/176, 188/186, 273/280, 396/413
+//   circle, m 128, every pixel   1.04, 1.02, 0.98, 0.96 of it
+//   circle, m 64, adaptive       0.99, 0.98, 0.98, 0.98; m 128: 1.03, 1.00, 0.98, 0.98
+//   6 blades, m 30, every pixel  247/182, 253/194, 339/292, 465/431
+//   6 blades, m 30, adaptive     142/125, 147/134, 158/154, 182/180
+// and with 3 to 16 blades, worst of them: every pixel m 3 0.94, 0.98, 0.98,
+// 1.00, m 4 0.97, 1.01, 1.01, 1.02; dilated m 6 0.97, 1.00, 0.99, 1.00, m 8
+// 1.01, 1.03, 1.00, 1.01; adaptive m 8 0.95, 0.98, 0.97, 0.99, m 12 1.04, 1.02,
+// 0.99, 1.00.
+bool compact_in_one(const FrameConst &fc)
+{
+    const int64_t np = (int64_t)fc.hw * fc.hh;
+    if (np > kSmallFrame) return false;
+    const bool adaptive = fc.mask_mode == DOF_MASK_ADAPTIVE, dilate = fc.mask_mode == DOF_MASK_DILATE;
+    if (fc.ap.blades >= 3) return fc.m <= (adaptive ? 8 : (dilate ? 6 : 3));
+    return np >= kSmallFrame / 2 || fc.m <= (adaptive ? 64 : 24);
+}
+
 }  // namespace
 
 #define DOF_REC(k)                                          \
@@ -1926,7 +1950,7 @@ hipError_t launch_frame_pre(const FrameConst &fc, const Rings &rings, const Scra
     }
     DOF_REC(6);
     hipError_t e;
-    if (np <= kSmallFrame && reinterpret_cast<uintptr_t>(mask) % 4 == 0) {
+    if (compact_in_one(fc) && reinterpret_cast<uintptr_t>(mask) % 4 == 0) {
         e = launch_compact_small(fc, L, scratch, mask, st);
     } else {
         k_compact_count<<<(unsigned)L.nchunks, 256, 0, st>>>(np, mask, P);

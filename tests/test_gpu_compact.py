@@ -55,3 +55,15 @@ def test_queue_and_rays(env, orc, w, h, m, mode, blades, offset):
     assert np.array_equal(d["queue"], want["queue"]) and np.array_equal(d["ray_base"], want["ray_base"])
     assert np.array_equal(d["ray_hit"], want["ray_hit"])
     assert np.array_equal(d["ray_t"].view(np.uint32), want["ray_t"].view(np.uint32))
+
+
+# either side of the rays per pixel up to which the one launch does it, which
+# depend on the aperture and the mask's mode, and of the size from which a
+# circular aperture's have no bound (65536 half-res pixels)
+@pytest.mark.parametrize("w,h,m,mode,blades", [
+    (66, 62, 8, synth.MASK_ADAPTIVE, 3), (66, 62, 9, synth.MASK_ADAPTIVE, 3), (66, 62, 6, synth.MASK_DILATE, 16),
+    (66, 62, 7, synth.MASK_DILATE, 16), (66, 62, 3, synth.MASK_FIXED, 6), (66, 62, 4, synth.MASK_FIXED, 6),
+    (66, 62, 64, synth.MASK_ADAPTIVE, 0), (66, 62, 65, synth.MASK_ADAPTIVE, 0), (66, 62, 24, synth.MASK_ALL, 0),
+    (66, 62, 25, synth.MASK_ALL, 0), (512, 512, 25, synth.MASK_FIXED, 0), (510, 514, 25, synth.MASK_FIXED, 0)])
+def test_either_way_of_compacting(env, orc, w, h, m, mode, blades):
+    test_queue_and_rays(env, orc, w, h, m, mode, blades, 0)
