@@ -1,7 +1,7 @@
 """The tree at the leaf counts where its build changes: one block of leaves
 and the next, the one-workgroup sort's last, the block count up to which one
-workgroup merges all exits, the sort's two tile sizes; and scenes whose keys
-are all equal (ties in reference order).  Keys, references, children, parents
+workgroup merges all exits, the counts at which the sort's tiles grow; and
+scenes whose keys are all equal (ties in reference order).  Keys, references, children, parents
 and child boxes equal the oracle's bit for bit (exact: no tolerance)."""
 
 import numpy as np
@@ -61,3 +61,11 @@ def test_tree_at_the_edges_of_the_build(orc, n, kind):
     tris = view["tris"].reshape(n, 12)
     assert np.array_equal(tris[:, 3].view(np.uint32), ob["ids"])
     assert np.array_equal(tris[:, [0, 1, 2, 4, 5, 6, 8, 9, 10]], sc.verts[ob["ids"]])
+
+
+# the sort's tiles are of 2048 keys up to 131072, of 4096 up to 1048576, of 8192
+# beyond: full tiles, and a last one of a single key
+@pytest.mark.parametrize("n,kind", [(131072, "soup"), (131073, "soup"), (1048576, "soup"), (1048577, "soup"),
+                                    (1048577, "equal")])
+def test_tree_where_the_sorts_tiles_grow(orc, n, kind):
+    test_tree_at_the_edges_of_the_build(orc, n, kind)
