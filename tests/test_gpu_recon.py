@@ -97,3 +97,72 @@ def test_circle_of_confusion_that_is_no_number(envs, w, h):
     nan = np.isnan(t1[..., 0])
     assert nan[:16, :16].all() and (d["var_blur"].reshape(nan.shape)[:16, :16] > 0).all()
     assert np.array_equal(rec[nan][:, :3], med[nan][:, :3]) and np.array_equal(rec[nan][:, 3], t1[nan][:, 1])
+
+
+def _wild(fr):
+    """The mark of a frame whose colours may sum to no number (third counter)."""
+    import ctypes as C
+    import torch
+    from paper_2210_06158_amd import dof
+    v = dof.DofDebugView()
+    dof.check(dof.lib().dof_debug_view_get(C.c_void_p(fr.scratch.data_ptr()), fr.W, fr.H, C.byref(fr.ps), C.byref(v)))
+    return int(fr._view(v.counters - fr.scratch.data_ptr(), 12, torch.int32).cpu()[2])
+
+
+@pytest.mark.parametrize("w,h", [(32, 32), (130, 40), (896, 896)])
+@pytest.mark.parametrize("batch", [False, True])
+def test_sums_that_overflow(envs, orc, batch, w, h):
+    """Colours of 1e37: the median is finite, but the sum over a pixel's taps
+    often is not, and 0 times it is no 0, so pixels of weight 0 read their taps
+    here too.  Where a sum overflows is the oracle's, but for pixels that a
+    colour 2e-5 larger or smaller (twice the taps' rounding) decides otherwise.
+    The next frame in the same buffers is an ordinary one."""
+    import torch
+    from paper_2210_06158_amd import dof
+    env, cam, lens, params = envs[1.0]
+    base = synth.scene_small()[0]
+    cam = dataclasses.replace(cam, width=w, height=h)
+    p = dataclasses.replace(params, mask_mode=synth.MASK_ALL, var_recon_w=2.0)
+    want = []
+    for scale in (1e37, 1e37 * (1 - 2e-5), 1e37 * (1 + 2e-5)):
+        sc = dataclasses.replace(base, albedo=(base.albedo * scale).astype(np.float32))
+        osc = orc.OracleScene(sc)
+        osc.build_bvh()
+        gb = orc.gbuffer(osc, cam, lens)
+        want.append((sc, gb, orc.render_frame(osc, cam, lens, p, gb)))
+    print(f"{w}x{h} batch {batch}", flush=True)
+    sc, gb, o = want[0]
+    wild = dof.Scene(sc)
+    wild.build_bvh()
+    fr = dof.Frame(w, h, p, ray_records=True)
+    hist = dof.history_alloc(w, h)
+
+    def frame(gs, gb):
+        g = tuple(torch.from_numpy(x).cuda() for x in (gb.colour, gb.depth, gb.normal))
+        if batch:
+            b = dof.Batch(1, p, ray_records=True)
+            b.set([fr.item(gs, cam, lens, g, None, hist)])
+            b.run()
+        else:
+            fr.render(gs, cam, lens, g, None, hist)
+        torch.cuda.synchronize()
+        return fr.debug()
+
+    d = frame(wild, gb)
+    assert _wild(fr) != 0
+    got, exp = d["recon"], o["recon"].reshape(d["recon"].shape)
+    fin = [np.isfinite(x[2]["recon"].reshape(got.shape)) for x in want]
+    sure = (fin[1] == fin[2]) & (fin[0] == fin[1])
+    assert (sure & ~fin[0])[..., :3].any() and (sure & fin[0])[..., :3].any() and sure.mean() > 0.999
+    assert np.array_equal(np.isnan(got)[sure], np.isnan(exp)[sure]) and np.array_equal(np.isfinite(got)[sure], fin[0][sure])
+    at = (sure & fin[0])[..., :3]
+    med = d["rtmed"].reshape(got.shape)[..., :3]
+    assert np.array_equal(got[..., :3][at], med[at])     # weight 0: luma variances of infinity minus infinity count as 0
+    np.testing.assert_allclose(got[..., :3][at], exp[..., :3][at], rtol=1e-5, atol=0)
+    np.testing.assert_allclose(got[..., 3], exp[..., 3], rtol=1e-5, atol=1e-5)
+
+    gb = orc.gbuffer(env["osc"], cam, lens)
+    o = orc.render_frame(env["osc"], cam, lens, p, gb)
+    d = frame(env["gs"], gb)
+    assert _wild(fr) == 0
+    np.testing.assert_allclose(d["recon"], o["recon"], rtol=1e-5, atol=1e-5)
