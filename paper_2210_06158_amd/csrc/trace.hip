@@ -512,11 +512,13 @@ __global__ __launch_bounds__(256) void k_gbuffer_shade(SceneArgs S, SceneShade s
 {
     const uint32_t p = blockIdx.x * 256u + threadIdx.x;
     if (p >= npx) return;
-    const uint32_t leaf = src.normal[(size_t)p * src.stride];
-    if (leaf != ~0u) {
+    const float t = src.depth[p];
+    if (t < INFINITY) {
+        // a caller may hand in one piece of memory for the two images it does
+        // not want: the leaf's bound keeps the reads inside the scene then
+        const uint32_t leaf = min(src.normal[(size_t)p * src.stride], (uint32_t)S.nleaf - 1u);
         float o[3], d[3];
         src.ray(p, o, d);
-        const float t = src.depth[p];
         const ViewConst &v = src.view;
         const float P0 = o[0] + t * d[0], P1 = o[1] + t * d[1], P2 = o[2] + t * d[2];
         const Shaded s = dof::shade(load_leaf(S, leaf), sh, d);

@@ -106,3 +106,27 @@ def test_counters_of_a_scene_of_one_leaf(batch, leaf_batch):
         w = fr.stats.cpu().numpy().view(np.uint32)
         rays, (visits, tests) = int(w[1]), (int(x) for x in w[2:6].view(np.uint64))
     assert (rays, visits, tests) == (33 * 25 * 5, 0, 33 * 25 * 5)
+
+
+@pytest.mark.parametrize("w,h", [(34, 18), (512, 512)])
+@pytest.mark.parametrize("formats", [("f32", "f16"), ("f16", "f32"), ("f32", "f32")])
+def test_depth_beside_images_in_one_memory(w, h, formats):
+    """A program that wants the depths alone may pass one buffer for both
+    images; the depths are those of separate buffers (exact)."""
+    import dataclasses
+    import torch
+    from paper_2210_06158_amd import dof
+    scene, cam, lens, _ = synth.scene_small()
+    cam = dataclasses.replace(cam, width=w, height=h)
+    gs = dof.Scene(scene)
+    gs.build_bvh()
+    want = gs.render_gbuffer(cam, lens)[1]
+    whole = torch.zeros(w * h * 4, dtype=torch.float32, device="cuda")
+    img = {"f32": whole.view(h, w, 4), "f16": whole.view(torch.float16)[:w * h * 4].view(h, w, 4)}
+    depth = torch.zeros((h, w), device="cuda")
+    print(f"{w}x{h} {formats}", flush=True)
+    for _ in range(2):
+        gs.render_gbuffer_into(cam, lens, img[formats[0]], depth, img[formats[1]])
+    torch.cuda.synchronize()
+    assert torch.isfinite(want).any()
+    assert torch.equal(depth.view(torch.int32), want.view(torch.int32))
