@@ -733,7 +733,6 @@ __device__ inline uint32_t merge_entries(MergeLds &m, const TreeOut &T, int coun
             }
             split = s;
             // union(left, right) as compare-selects, left first
-#pragma unroll
             for (int a = 0; a < 3; ++a) {
                 const float L = m.box[a][s], R = m.box[6 + a][s], LH = m.box[3 + a][s], RH = m.box[9 + a][s];
                 lo[a] = R < L ? R : L;

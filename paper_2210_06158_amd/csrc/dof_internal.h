@@ -283,12 +283,12 @@ int trace_blocks_per_cu(bool batch, int stack, int steps);   // resident blocks 
 int blocks_for(int blocks, int64_t rays);   // of `blocks`, as many as a launch of at most `rays` rays has work for
 hipError_t launch_trace(const SceneDev &s, const FrameConst &fc, const ScratchLayout &L, char *scratch,
                         int blocks, hipStream_t st);
-// the ray records of every thin-lens ray of the frame (after the compaction)
 // compaction and ray generation of a frame of at most kSmallFrame half-res
 // pixels, its mask aligned to 4 bytes
 hipError_t launch_compact_small(const FrameConst &fc, const ScratchLayout &L, char *scratch, const uint8_t *mask, hipStream_t st);
+// the ray records of every thin-lens ray of the frame (after the compaction)
 hipError_t launch_raygen(const FrameConst &fc, const ScratchLayout &L, char *scratch, hipStream_t st);
-// hit record, distance, shaded colour and position of every ray (after the traversal)
+
 // Job of a block of a batched launch: the last job whose first block in grid
 // g is at or before b; (bx, by) is the block within that job's own grid.
 __device__ inline int job_of_block(const Job *__restrict__ jobs, int njobs, int g, uint32_t b, uint32_t &bx,

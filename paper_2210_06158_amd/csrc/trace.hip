@@ -389,9 +389,6 @@ __device__ inline void lens_shade(const LeafData &data, const FrameConst &fc, co
     }
 }
 
-// Ray records (three float4 planes): (o, d.x), (d.y, d.z, sx, sy),
-// (sz, 1/d.x, 1/d.y, 1/d.z), written by the ray generation kernel so that a
-// traversal lane takes a new ray with three independent loads.
 // A ray record is its origin and direction (24 B: a float4 and a float2
 // plane); the traversal derives the watertight shear and the reciprocals when
 // a lane takes the ray (six correctly rounded divides, shared by the lanes a
@@ -706,7 +703,7 @@ __global__ __launch_bounds__(kGenTB) void kb_raygen(const Job *__restrict__ jobs
 // instead of the three kernels' 13 and two gaps.  256x256 113 -> 109 us a
 // frame, 640x480 144 -> 137, 800x600 159 -> 154; the sums over the mask grow
 // with the square of the frame, and at 960x960 (230400 half-res pixels) it is
-// 218 -> 220: hence kSmallFrame.
+// 218 -> 220: hence kSmallFrame.  compact_in_one says which frames take it.
 constexpr int kSmallRays = 4096;   // rays of a window (16 per pixel)
 
 __global__ __launch_bounds__(kGenTB) void k_compact_small(FrameConst fc, Planes P, const uint8_t *__restrict__ mask)
@@ -876,20 +873,6 @@ constexpr int kDropChunk = 8;    // oldest stack entries dropped when the LDS st
 // persistent grid hands out set its tail: when they are cheap, every wave
 // finishes at nearly the same time.
 
-// work: slot 0 of the work-counter slots; stats and drops_out (or null):
-// slot 0's node-visit and stack-drop statistics, a wave adding its totals to
-// the slot of its block (b mod kWorkParts) when it finishes.
-// What bounds it: at 3840x2160 the L1's lookups (0.9 a cycle and CU, the
-// texture data unit busy 0.95 of the time); at 1920x1080, with 2.4 rays per
-// lane, also the waves' uneven ends.  A visit takes about 50 vector
-// instructions, where predicates kept as booleans in registers, index
-// arithmetic for the stack and 64-bit node addresses made it 74: gathered over
-// the launch 763 M instead of 949 M vector instructions at 4K, the traversal
-// 1358 -> 1215 us there and 349 -> 240 us at 1080p (with the work sharing).
-// Occupancy: 70 VGPRs a lane would let seven waves share a SIMD; the 24-entry
-// stack's LDS allows six (12.5 KB a block), the 16-entry one's seven.  A
-// batch's lanes also hold their scene's pointers; asking for six waves (80
-// VGPRs) makes a 32-session batch 3.6 % faster.
 // Orders a wave's own LDS accesses (they execute in order; this keeps the
 // compiler from moving or caching them).
 __device__ inline void wave_sync()
@@ -905,6 +888,20 @@ __device__ inline LdsWord *lds_word(uint32_t address) { return (LdsWord *)(uintp
 // A lane mask as each lane's predicate.
 __device__ inline bool lanes(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
 
+// work: slot 0 of the work-counter slots; stats and drops_out (or null):
+// slot 0's node-visit and stack-drop statistics, a wave adding its totals to
+// the slot of its block (b mod kWorkParts) when it finishes.
+// What bounds it: at 3840x2160 the L1's lookups (0.9 a cycle and CU, the
+// texture data unit busy 0.95 of the time); at 1920x1080, with 2.4 rays per
+// lane, also the waves' uneven ends.  A visit takes about 50 vector
+// instructions, where predicates kept as booleans in registers, index
+// arithmetic for the stack and 64-bit node addresses made it 74: gathered over
+// the launch 763 M instead of 949 M vector instructions at 4K, the traversal
+// 1358 -> 1215 us there and 349 -> 240 us at 1080p (with the work sharing).
+// Occupancy: 70 VGPRs a lane would let seven waves share a SIMD; the 24-entry
+// stack's LDS allows six (12.5 KB a block), the 16-entry one's seven.  A
+// batch's lanes also hold their scene's pointers; asking for six waves (80
+// VGPRs) makes a 32-session batch 3.6 % faster.
 // kFar: the nodes' byte offsets need more than 32 bits (kMaxNear leaves)
 template <class Src, int kStack, int kSteps, bool kFar>
 __global__ __launch_bounds__(kTB) __attribute__((amdgpu_waves_per_eu(Src::kPerLaneScene ? (kStack == 32 ? 1 : 6) : (kStack == 16 ? 7 : 1))))

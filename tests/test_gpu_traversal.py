@@ -28,7 +28,7 @@ def scenes(orc):
 
 
 # 1 ray; one wave's lanes and its neighbours; a few rays per wave; the default
-# grid's lanes at six blocks of 128 per SIMD (393216) and one more
+# grid's lanes at six waves per SIMD (393216) and one more
 @pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 1000, 4097, 393215, 393216, 393217])
 @pytest.mark.parametrize("name", ["soup", "one", "ladder"])
 def test_rays_at_the_edges_of_the_hand_out(scenes, orc, name, n):
